@@ -298,6 +298,24 @@ struct AxisOp {
   double h;
   double2 kLo, kHi;  // K corner entries times h
 };
+// State of a refinement that the device controls (captured solves), and the
+// rule applied to the norms of one residual launch (c null: norms only).
+struct IrCtl {
+  int done;        // nonzero: converged or failed, later launches return at once
+  int iters;       // refinement steps taken after the first solve
+  int status;      // HELM_* of the solve
+  int pad;
+  double rel_first;
+  double rel_last;
+};
+struct IrCheck {
+  IrCtl* c = nullptr;
+  IrCtl* mirror = nullptr;  // pinned host copy of the state, written with it
+  double tol = 0;
+  int max_steps = 0;        // step count at which the check declares non-convergence
+  int stage = 0;            // 0: after the first solve
+};
+
 struct ResidArgs {
   int dim, nb;
   AxisOp ax[3];
@@ -310,6 +328,10 @@ struct ResidArgs {
   double* scratch;
   int64_t scratch_len;
   const int* skip = nullptr;  // device flag: nothing is computed while *skip != 0
+  // Arrival counter (zero before and after every launch), for launches that
+  // finish their norms themselves; null: always a separate finish.
+  unsigned* counter = nullptr;
+  IrCheck check;
 };
 hipError_t launch_residual(const ResidArgs& a, hipStream_t s);
 int64_t residual_scratch_len(int dim, const int64_t* grid, int nb);

@@ -139,6 +139,9 @@ struct helm_plan {
   const double2* sig[4] = {nullptr, nullptr, nullptr, nullptr};
   // device-side refinement control (IrCtl) for captured solves
   helm::DevMem ctl;
+  // arrival counter of the residual launches (zeroed at setup; every launch
+  // leaves it zero)
+  helm::DevMem res_count;
   int dense = 0;  // 1: periodised axes use the dense eigenvector transforms
   // Boundary operator tables (3D, helm_options.boundary): capW holds the
   // inner Step-2 map of every outer periodic mode l (line family (B, A)),
@@ -1361,6 +1364,7 @@ ResidArgs resid_args(helm_plan* p, int nb) {
   a.norms = p->norms.as<double>();
   a.scratch = p->scratch.as<double>();
   a.scratch_len = (int64_t)(p->scratch.bytes / sizeof(double));
+  a.counter = p->res_count.as<unsigned>();
   a.r = nullptr;
   a.r_kind = ST_C128;
   return a;
@@ -1482,63 +1486,13 @@ void fill_axis_tables_host(PAxis& a, long double czx, std::vector<double2>& buf,
 // kernel evaluates them and raises a flag that turns every later launch of
 // the same problem into an immediate return.
 // ---------------------------------------------------------------------------
-struct IrCtl {
-  int done;        // nonzero: converged or failed, later launches return at once
-  int iters;       // refinement steps taken after the first solve
-  int status;      // HELM_* of the solve
-  int pad;
-  double rel_first;
-  double rel_last;
-};
-
-__global__ void ir_reset_kernel(IrCtl* c, int done, IrCtl* mirror) {
+__global__ void ir_reset_kernel(IrCtl* c, int done) {
   c->done = done;
   c->iters = 0;
   c->status = HELM_OK;
   c->pad = 0;
   c->rel_first = -1.0;
   c->rel_last = -1.0;
-  if (mirror) *mirror = *c;
-}
-
-// After the residual of stage k (k = 0: first solve): converged, failed or
-// one more refinement step.  Same rule as the host loop of helm_solve: stop
-// at tol, at max_iter steps, or when a step fails to halve the residual.
-__device__ void ir_update(const double* norms, int nb, double tol, int max_steps, int stage, IrCtl* c) {
-  double mx = 0.0;
-  bool bad = false;
-  for (int b = 0; b < nb; ++b) {
-    const double rr = norms[2 * b], ff = norms[2 * b + 1];
-    if (!isfinite(rr) || !isfinite(ff)) bad = true;
-    const double v = ff > 0.0 ? sqrt(rr / ff) : 0.0;
-    mx = fmax(mx, v);
-  }
-  if (bad) {
-    c->status = HELM_ENONFINITE;
-    c->rel_last = NAN;
-    c->done = 1;
-    return;
-  }
-  const double prev = c->rel_last;
-  if (stage == 0) c->rel_first = mx;
-  c->rel_last = mx;
-  if (mx <= tol) {
-    c->status = HELM_OK;
-    c->done = 1;
-  } else if (stage >= max_steps || (stage > 0 && !(mx < 0.5 * prev))) {
-    c->status = HELM_ENOCONV;
-    c->done = 1;
-  } else {
-    c->iters = stage + 1;
-  }
-}
-
-// With `mirror` set, the resulting state is also written there (pinned host
-// memory that the host reads after the stream has drained).
-__global__ void ir_check_kernel(const double* norms, int nb, double tol, int max_steps, int stage, IrCtl* c,
-                                IrCtl* mirror) {
-  if (!c->done) ir_update(norms, nb, tol, max_steps, stage, c);
-  if (mirror) *mirror = *c;
 }
 
 // Enqueue one problem's complete solve with `steps` refinement steps whose
@@ -1553,13 +1507,21 @@ int enqueue_device_ir(helm_plan* p, const double2* F, double2* U, int nb, int st
   const bool mixed = p->opt.precision == HELM_PREC_MIXED;
   const bool check = mixed || p->opt.check;
   IrCtl* c = p->ctl.as<IrCtl>();
+  // A solve captured for its plan alone needs no reset launch (stage 0 of the
+  // check initialises the control block, and no launch before it reads that)
+  // and finishes its norms in the residual launch.  Branches of a batch graph
+  // keep the reset and the separate finish: they overlap, so the launches cost
+  // nothing there, and an unchecked problem's report needs the reset.
+  const bool batch = mirror == nullptr;
   const bool prof = p->prof;
   p->prof = false;
   p->skip_cur = nullptr;
   int rc = HELM_OK;
   do {
-    hipLaunchKernelGGL(ir_reset_kernel, dim3(1), dim3(1), 0, st, c, check ? 0 : 1, mirror);
-    if (hipGetLastError() != hipSuccess) { rc = HELM_EDEVICE; break; }
+    if (batch) {
+      hipLaunchKernelGGL(ir_reset_kernel, dim3(1), dim3(1), 0, st, c, check ? 0 : 1);
+      if (hipGetLastError() != hipSuccess) { rc = HELM_EDEVICE; break; }
+    }
     rc = solve_once(p, F, ST_C128, U, 0, nb, mixed, st);
     if (rc || !check) break;
     const int rk = mixed ? ST_C64 : ST_C128;
@@ -1576,10 +1538,9 @@ int enqueue_device_ir(helm_plan* p, const double2* F, double2* U, int nb, int st
       a.f = F;
       a.r = k < steps ? p->R.p : nullptr;
       a.r_kind = rk;
-      if (launch_residual(a, st) != hipSuccess) { rc = HELM_EDEVICE; break; }
-      hipLaunchKernelGGL(ir_check_kernel, dim3(1), dim3(1), 0, st, (const double*)a.norms, nb, p->opt.tol,
-                         limit, k, c, mirror);
-      if (hipGetLastError() != hipSuccess) rc = HELM_EDEVICE;
+      a.check = IrCheck{c, mirror, p->opt.tol, limit, k};
+      if (batch) a.counter = nullptr;
+      if (launch_residual(a, st) != hipSuccess) rc = HELM_EDEVICE;
     }
   } while (false);
   p->skip_cur = nullptr;
@@ -2757,6 +2718,9 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
     if (crc != HELM_OK) return crc;
   }
   if (prepare_roots(p.get()) != HELM_OK) return HELM_ENOMEM;
+  HCHK(p->res_count.ensure(sizeof(unsigned)));
+  const unsigned zero = 0;
+  HCHK(upload(p->res_count.p, &zero, sizeof zero));
   if (hipHostMalloc(reinterpret_cast<void**>(&p->h_norms_pin), 2 * HELM_STATIC_MAX_RHS * sizeof(double),
                     hipHostMallocDefault) != hipSuccess) {
     p->h_norms_pin = nullptr;

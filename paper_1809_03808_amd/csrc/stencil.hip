@@ -3,10 +3,9 @@
 // the 1D entries of eqs. (matrixK), (matrixM)), and per right-hand side the
 // squared norms sum |r|^2 and sum |f|^2 used by iterative refinement.
 //
-// Each thread produces four consecutive nodes along the contiguous axis.  For
-// every stencil row (3 in 2D, 9 in 3D) it loads the six values it needs once
-// and applies the last-axis 1D operators M and K to them; the row results are
-// combined with the products of the leading-axis 1D entries:
+// The kernels stream strips of the leading axis: every row (plane) of u is
+// loaded once and the last-axis 1D operators M and K applied to it; the results
+// of three consecutive rows (planes) are combined with the leading-axis entries:
 //   2D:  (A u)_x = sum_{o1} S1(o1) (M2 u_{o1})_x + M1(o1) (K2 u_{o1})_x,
 //   3D:  (A u)_x = sum_{o1,o2} [S1 M2 + M1 K2](o1,o2) (M3 u_{o1,o2})_x
 //                              + M1(o1) M2(o2) (K3 u_{o1,o2})_x,
@@ -22,27 +21,7 @@ namespace helm {
 namespace {
 
 constexpr int kResThreads = 256;
-constexpr int kQuad = 4;
 constexpr int kFinThreads = 1024;
-
-// (M u)_x and (K u)_x for the 4 outputs x0..x0+3 of one row whose values
-// v[0..5] are u[x0-1 .. x0+4] (zero outside the line).
-__device__ inline void row_ops(const double2* v, int n, double h, double2 kLo, double2 kHi, int x0,
-                               double2* Mv, double2* Kv) {
-#pragma unroll
-  for (int j = 0; j < kQuad; ++j) {
-    const int x = x0 + j;
-    double2 m = make_double2(0, 0), k = make_double2(0, 0);
-#pragma unroll
-    for (int o = -1; o <= 1; ++o) {
-      const double2 u = v[j + 1 + o];
-      m = cadd(m, cscale(u, m1d(n, h, x, o)));
-      k = cfma(k1d(n, h, kLo, kHi, x, o), u, k);
-    }
-    Mv[j] = m;
-    Kv[j] = k;
-  }
-}
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Renumber them so that every XCD works on one contiguous range of
@@ -53,112 +32,120 @@ __device__ inline int64_t xcd_contiguous(int64_t b, int64_t n) {
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-template <typename TR>
-__global__ __launch_bounds__(kResThreads) void residual_kernel(ResidArgs a, int64_t per_rhs,
-                                                               int64_t quads_per_rhs, int64_t blocks_per_rhs) {
-  __shared__ double red[2][kResThreads];
-  if (a.skip && *a.skip) return;
-  const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int64_t b = bid / blocks_per_rhs;
-  const int64_t qi = (bid % blocks_per_rhs) * kResThreads + threadIdx.x;
-  double sr = 0.0, sf = 0.0;
-  if (qi < quads_per_rhs) {
-    const int dim = a.dim;
-    const AxisOp& AL = a.ax[dim - 1];  // contiguous axis
-    const int nL = AL.n;
-    const int nq = (nL + kQuad - 1) / kQuad;
-    const int64_t rowi = qi / nq;           // index of the line (i1 or i1*n2+i2)
-    const int x0 = (int)(qi - rowi * nq) * kQuad;
-    const int64_t off = b * per_rhs;
-    double2 au[kQuad];
-#pragma unroll
-    for (int j = 0; j < kQuad; ++j) au[j] = make_double2(0, 0);
-    const AxisOp& A1 = a.ax[0];
-    if (dim == 2) {
-      const int i1 = (int)rowi;
-      for (int o1 = -1; o1 <= 1; ++o1) {
-        const double m1 = m1d(A1.n, A1.h, i1, o1);
-        if (m1 == 0.0) continue;
-        const double2 k1 = k1d(A1.n, A1.h, A1.kLo, A1.kHi, i1, o1);
-        const double2 s1 = make_double2(k1.x - a.w2 * m1, k1.y);
-        const double2* row = a.u + off + (int64_t)(i1 + o1) * nL;
-        double2 v[kQuad + 2];
-#pragma unroll
-        for (int j = 0; j < kQuad + 2; ++j) {
-          const int x = x0 - 1 + j;
-          v[j] = (x >= 0 && x < nL) ? row[x] : make_double2(0, 0);
-        }
-        double2 Mv[kQuad], Kv[kQuad];
-        row_ops(v, nL, AL.h, AL.kLo, AL.kHi, x0, Mv, Kv);
-#pragma unroll
-        for (int j = 0; j < kQuad; ++j) au[j] = cadd(cfma(s1, Mv[j], au[j]), cscale(Kv[j], m1));
-      }
+// Refinement control after the residual of stage k (k = 0: first solve), on
+// the device for captured solves: converged, failed or one more step.  The
+// rule of the host loop: stop at tol, at max_steps steps, or when a step fails
+// to halve the residual.  Stage 0 initialises the state.
+__device__ void ir_update(const double* norms, int nb, const IrCheck& k) {
+  IrCtl* c = k.c;
+  double mx = 0.0;
+  bool bad = false;
+  for (int b = 0; b < nb; ++b) {
+    const double rr = norms[2 * b], ff = norms[2 * b + 1];
+    if (!isfinite(rr) || !isfinite(ff)) bad = true;
+    const double v = ff > 0.0 ? sqrt(rr / ff) : 0.0;
+    mx = fmax(mx, v);
+  }
+  if (k.stage == 0) {
+    c->done = 0;
+    c->iters = 0;
+    c->status = HELM_OK;
+    c->pad = 0;
+    c->rel_first = -1.0;
+    c->rel_last = -1.0;
+  }
+  if (bad) {
+    c->status = HELM_ENONFINITE;
+    c->rel_last = NAN;
+    c->done = 1;
+  } else {
+    const double prev = c->rel_last;
+    if (k.stage == 0) c->rel_first = mx;
+    c->rel_last = mx;
+    if (mx <= k.tol) {
+      c->status = HELM_OK;
+      c->done = 1;
+    } else if (k.stage >= k.max_steps || (k.stage > 0 && !(mx < 0.5 * prev))) {
+      c->status = HELM_ENOCONV;
+      c->done = 1;
     } else {
-      const AxisOp& A2 = a.ax[1];
-      const int i1 = (int)(rowi / A2.n), i2 = (int)(rowi % A2.n);
-      for (int o1 = -1; o1 <= 1; ++o1) {
-        const double m1 = m1d(A1.n, A1.h, i1, o1);
-        if (m1 == 0.0) continue;
-        const double2 k1 = k1d(A1.n, A1.h, A1.kLo, A1.kHi, i1, o1);
-        const double2 s1 = make_double2(k1.x - a.w2 * m1, k1.y);
-        for (int o2 = -1; o2 <= 1; ++o2) {
-          const double m2 = m1d(A2.n, A2.h, i2, o2);
-          if (m2 == 0.0) continue;
-          const double2 k2 = k1d(A2.n, A2.h, A2.kLo, A2.kHi, i2, o2);
-          // coefficient of (M3 u_row): S1 M2 + M1 K2; of (K3 u_row): M1 M2
-          const double2 cm = make_double2(s1.x * m2 + m1 * k2.x, s1.y * m2 + m1 * k2.y);
-          const double ck = m1 * m2;
-          const double2* row = a.u + off + ((int64_t)(i1 + o1) * A2.n + (i2 + o2)) * nL;
-          double2 v[kQuad + 2];
-#pragma unroll
-          for (int j = 0; j < kQuad + 2; ++j) {
-            const int x = x0 - 1 + j;
-            v[j] = (x >= 0 && x < nL) ? row[x] : make_double2(0, 0);
-          }
-          double2 Mv[kQuad], Kv[kQuad];
-          row_ops(v, nL, AL.h, AL.kLo, AL.kHi, x0, Mv, Kv);
-#pragma unroll
-          for (int j = 0; j < kQuad; ++j) au[j] = cadd(cfma(cm, Mv[j], au[j]), cscale(Kv[j], ck));
-        }
-      }
-    }
-    const int64_t base = off + rowi * nL;
-#pragma unroll
-    for (int j = 0; j < kQuad; ++j) {
-      const int x = x0 + j;
-      if (x < nL) {
-        const double2 fv = a.f[base + x];
-        const double2 r = csub(fv, au[j]);
-        if (a.r) reinterpret_cast<TR*>(a.r)[base + x] = from_d2<TR>(r);
-        sr += r.x * r.x + r.y * r.y;
-        sf += fv.x * fv.x + fv.y * fv.y;
-      }
+      c->iters = k.stage + 1;
     }
   }
-  red[0][threadIdx.x] = sr;
-  red[1][threadIdx.x] = sf;
+  if (k.mirror) *k.mirror = *c;
+}
+
+// Norm partials of a block (NT values each of red[0], red[1]) to scratch, and
+// with a counter the whole finish in the block that arrives last: it sums the
+// partials of every right-hand side in a fixed order (so the result does not
+// depend on which block that is), writes the norms and applies the refinement
+// rule.  That takes the launches after the residual (about 4.5 us each, the
+// floor of a graph node) out of a small solve.
+// Ordering across the XCDs: the partials are agent-scope atomic stores, which
+// write through the XCD's L2, and the wave waits for them before it counts its
+// block; the last block reads them with agent-scope atomic loads.  A release
+// fence instead of the wait writes back the whole L2 once per block (4096^2
+// mixed: 139 -> 227 us per launch).
+template <int NT>
+__device__ inline void finish_norms(const ResidArgs& a, double (*red)[NT], double sr, double sf, int64_t bid,
+                                    int64_t blocks_per_rhs) {
+  const int tid = threadIdx.x;
+  red[0][tid] = sr;
+  red[1][tid] = sf;
   __syncthreads();
-  for (int s = kResThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + s];
-      red[1][threadIdx.x] += red[1][threadIdx.x + s];
+  for (int st = NT / 2; st > 0; st >>= 1) {
+    if (tid < st) {
+      red[0][tid] += red[0][tid + st];
+      red[1][tid] += red[1][tid + st];
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    a.scratch[2 * bid] = red[0][0];
-    a.scratch[2 * bid + 1] = red[1][0];
+  __shared__ int last;
+  if (tid == 0) {
+    __hip_atomic_store(a.scratch + 2 * bid, red[0][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.scratch + 2 * bid + 1, red[1][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.counter) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const unsigned n = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = n + 1 == gridDim.x;
+    }
+  }
+  if (!a.counter) return;
+  __syncthreads();
+  if (!last) return;
+  const int lane = tid & 63, wv = tid >> 6;
+  for (int64_t b = wv; b < a.nb; b += NT / 64) {
+    double r = 0.0, f = 0.0;
+#pragma unroll 4
+    for (int64_t i = lane; i < blocks_per_rhs; i += 64) {
+      double* q = a.scratch + 2 * (b * blocks_per_rhs + i);
+      r += __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      f += __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+      r += __shfl_down(r, d);
+      f += __shfl_down(f, d);
+    }
+    if (lane == 0) {
+      a.norms[2 * b] = r;
+      a.norms[2 * b + 1] = f;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    *a.counter = 0;  // ready for the next launch
+    if (a.check.c) ir_update(a.norms, a.nb, a.check);
   }
 }
 
-// 2D: one thread per column x, a block streams down a strip of kStrip rows
+// 2D: one thread per column x, a block streams down a strip of rows
 // of 256 columns.  Each row of u is loaded once (consecutive lanes on
 // consecutive columns), its x_2 neighbours come from the adjacent lanes
 // (the two wave-edge lanes load theirs), and the row operators M_2 u_j and
 // K_2 u_j of rows i-1, i, i+1 stay in registers while the strip advances,
 // so u and f are read from memory once (plus two halo rows per strip).  The
 // rows one and two ahead are already in flight while row i is combined.
-constexpr int kStrip = 32;
+constexpr int kStrip = 32;  // longest strip
 
 struct RowRaw {
   double2 c, e;  // u[j][x], and u[j][x -/+ 1] for the first / last lane of the wave
@@ -166,7 +153,7 @@ struct RowRaw {
 
 template <typename TR>
 __global__ __launch_bounds__(kResThreads) void residual2d_kernel(ResidArgs a, int64_t xtiles,
-                                                                 int64_t blocks_per_rhs) {
+                                                                 int64_t blocks_per_rhs, int strip) {
   __shared__ double red[2][kResThreads];
   if (a.skip && *a.skip) return;
   const int64_t bid = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -179,7 +166,7 @@ __global__ __launch_bounds__(kResThreads) void residual2d_kernel(ResidArgs a, in
   const int x = (int)xi * kResThreads + (int)threadIdx.x;
   const bool xok = x < n2;
   const int lane = threadIdx.x & 63;
-  const int r0 = (int)si * kStrip, r1 = min(n1, r0 + kStrip);
+  const int r0 = (int)si * strip, r1 = min(n1, r0 + strip);
   const int64_t off = b * (int64_t)n1 * n2;
   const double2* U = a.u + off;
   const int xe = lane == 0 ? x - 1 : x + 1;  // edge neighbour loaded by the wave-edge lanes
@@ -238,20 +225,7 @@ __global__ __launch_bounds__(kResThreads) void residual2d_kernel(ResidArgs a, in
     Kc = Kn;
     nx = nn;
   }
-  red[0][threadIdx.x] = sr;
-  red[1][threadIdx.x] = sf;
-  __syncthreads();
-  for (int st = kResThreads / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + st];
-      red[1][threadIdx.x] += red[1][threadIdx.x + st];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    a.scratch[2 * bid] = red[0][0];
-    a.scratch[2 * bid + 1] = red[1][0];
-  }
+  finish_norms<kResThreads>(a, red, sr, sf, bid, blocks_per_rhs);
 }
 
 // 3D: a block of 8 waves owns an (x_2, x_3) tile of 8 rows x 64 columns and
@@ -393,20 +367,7 @@ __global__ __launch_bounds__(k3Threads) void residual3d_kernel(ResidArgs a, int6
     Qc = Qn;
     nx = nn;
   }
-  red[0][threadIdx.x] = sr;
-  red[1][threadIdx.x] = sf;
-  __syncthreads();
-  for (int st = k3Threads / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + st];
-      red[1][threadIdx.x] += red[1][threadIdx.x + st];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    a.scratch[2 * bid] = red[0][0];
-    a.scratch[2 * bid + 1] = red[1][0];
-  }
+  finish_norms<k3Threads>(a, red, sr, sf, bid, blocks_per_rhs);
 }
 
 __global__ __launch_bounds__(kFinThreads) void norm_finish_kernel(const double* scratch, int64_t blocks_per_rhs,
@@ -435,98 +396,91 @@ __global__ __launch_bounds__(kFinThreads) void norm_finish_kernel(const double* 
   }
 }
 
-void geometry(int dim, const int64_t* n, int64_t* per, int64_t* quads, int64_t* bpr) {
-  int64_t p = 1;
-  for (int j = 0; j < dim; ++j) p *= n[j];
-  const int64_t nL = n[dim - 1];
-  const int64_t lines = p / nL;
-  *per = p;
-  *quads = lines * ((nL + kQuad - 1) / kQuad);
-  *bpr = (*quads + kResThreads - 1) / kResThreads;
-}
-
 }  // namespace
 
-// 2D streaming geometry: column tiles of 256 and strips of kStrip rows.
-void geometry2d(const int64_t* n, int64_t* xtiles, int64_t* bpr) {
+// Strip length: the strip re-reads two halo rows (planes), so long strips move
+// less; short ones give more blocks and a shorter serial run per block.  The
+// longest strip (up to 32) that still gives `want` blocks, two or one per
+// compute unit (2D blocks have 256 threads, 3D ones 512), at least kStripMin.
+// With fixed strips of 32 a 128^2 residual was 4 blocks of 24.5 us (now 32 of
+// 8.8 us), 257^2 x 4 72 blocks of 26 us (520 of 16 us), 61x75x90 40 blocks of
+// 44.5 us (320 of 20 us); twice the blocks, or strips of 2, cost 0-2% per
+// solve at 2049^2 and 129^3.
+constexpr int kStripMin = 4;
+constexpr int64_t kWant2d = 512, kWant3d = 256;
+// Launches of at most this many blocks finish the norms in the last block; its
+// serial sum grows with the blocks, while the separate launches cost a fixed 9 us.
+constexpr int64_t kFusedBlocks = 4096;
+
+int pick_strip(int64_t tiles, int64_t n, int nb, int longest, int64_t want) {
+  int s = longest;
+  while (s > kStripMin && tiles * ((n + s - 1) / s) * nb < want) s >>= 1;
+  return s;
+}
+
+// 2D streaming geometry: column tiles of 256 and strips of rows.
+void geometry2d(const int64_t* n, int nb, int64_t* xtiles, int64_t* bpr, int* strip) {
   *xtiles = (n[1] + kResThreads - 1) / kResThreads;
-  *bpr = *xtiles * ((n[0] + kStrip - 1) / kStrip);
+  *strip = pick_strip(*xtiles, n[0], nb, kStrip, kWant2d);
+  *bpr = *xtiles * ((n[0] + *strip - 1) / *strip);
 }
 
 // 3D streaming geometry: 64-column x 8-row tiles, strips of 64 planes when
-// that leaves at least 4096 blocks (16 per compute unit), else of 32: a
-// strip re-reads two halo planes (512^3 x 16 residual: 18.6 ms with strips of
-// 32 planes, 18.1 with 64, 19.7 with 16).
+// that leaves at least 4096 blocks (16 per compute unit), else shorter (512^3
+// x 16 residual: 18.6 ms with strips of 32 planes, 18.1 with 64, 19.7 with 16).
 void geometry3d(const int64_t* n, int nb, int64_t* xtiles, int64_t* ytiles, int64_t* bpr, int* strip) {
   *xtiles = (n[2] + 63) / 64;
   *ytiles = (n[1] + k3Rows - 1) / k3Rows;
-  *strip = *xtiles * *ytiles * ((n[0] + 63) / 64) * nb >= 4096 ? 64 : kStrip;
-  *bpr = *xtiles * *ytiles * ((n[0] + *strip - 1) / *strip);
+  const int64_t tiles = *xtiles * *ytiles;
+  *strip = tiles * ((n[0] + 63) / 64) * nb >= 4096 ? 64 : pick_strip(tiles, n[0], nb, kStrip, kWant3d);
+  *bpr = tiles * ((n[0] + *strip - 1) / *strip);
 }
 
 int64_t residual_scratch_len(int dim, const int64_t* grid, int nb) {
-  int64_t per, quads, bpr;
-  geometry(dim, grid, &per, &quads, &bpr);
-  if (dim == 2) {
-    int64_t xt, b2;
-    geometry2d(grid, &xt, &b2);
-    bpr = std::max(bpr, b2);
-  } else {
-    int64_t xt, yt, b3;
-    int strip;
-    geometry3d(grid, nb, &xt, &yt, &b3, &strip);
-    bpr = std::max(bpr, b3);
-  }
+  int64_t xt, yt, bpr;
+  int strip;
+  if (dim == 2) geometry2d(grid, nb, &xt, &bpr, &strip);
+  else geometry3d(grid, nb, &xt, &yt, &bpr, &strip);
   return 2 * bpr * nb;
 }
 
-hipError_t launch_residual(const ResidArgs& a, hipStream_t s) {
+// The separate end of a residual launch of many blocks: norms, then the
+// refinement rule.
+__global__ void ir_check_kernel(const double* norms, int nb, IrCheck k, const int* skip) {
+  if (skip && *skip) return;
+  ir_update(norms, nb, k);
+}
+
+hipError_t launch_residual(const ResidArgs& a0, hipStream_t s) {
+  ResidArgs a = a0;
   int64_t n[3];
   for (int j = 0; j < a.dim; ++j) n[j] = a.ax[j].n;
-  int64_t per, quads, bpr;
-  if (a.dim == 2) {
-    int64_t xt;
-    geometry2d(n, &xt, &bpr);
-    const int64_t blocks = bpr * a.nb;
-    if (blocks > 0x7fffffffLL || 2 * blocks > a.scratch_len) return hipErrorInvalidValue;
-    if (a.r_kind == ST_C64)
-      hipLaunchKernelGGL(residual2d_kernel<float2>, dim3((unsigned)blocks), dim3(kResThreads), 0, s, a, xt, bpr);
-    else
-      hipLaunchKernelGGL(residual2d_kernel<double2>, dim3((unsigned)blocks), dim3(kResThreads), 0, s, a, xt, bpr);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(norm_finish_kernel, dim3((unsigned)a.nb), dim3(kFinThreads), 0, s, a.scratch, bpr, a.norms,
-                       a.skip);
-    return hipGetLastError();
-  }
-  {
-    int64_t xt, yt;
-    int strip;
-    geometry3d(n, a.nb, &xt, &yt, &bpr, &strip);
-    const int64_t blocks = bpr * a.nb;
-    if (blocks > 0x7fffffffLL || 2 * blocks > a.scratch_len) return hipErrorInvalidValue;
-    if (a.r_kind == ST_C64)
-      hipLaunchKernelGGL(residual3d_kernel<float2>, dim3((unsigned)blocks), dim3(k3Threads), 0, s, a, xt, yt, bpr,
-                         strip);
-    else
-      hipLaunchKernelGGL(residual3d_kernel<double2>, dim3((unsigned)blocks), dim3(k3Threads), 0, s, a, xt, yt, bpr,
-                         strip);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(norm_finish_kernel, dim3((unsigned)a.nb), dim3(kFinThreads), 0, s, a.scratch, bpr, a.norms,
-                       a.skip);
-    return hipGetLastError();
-  }
-  geometry(a.dim, n, &per, &quads, &bpr);
+  int64_t xt, yt = 1, bpr;
+  int strip;
+  if (a.dim == 2) geometry2d(n, a.nb, &xt, &bpr, &strip);
+  else geometry3d(n, a.nb, &xt, &yt, &bpr, &strip);
   const int64_t blocks = bpr * a.nb;
   if (blocks > 0x7fffffffLL || 2 * blocks > a.scratch_len) return hipErrorInvalidValue;
-  if (a.r_kind == ST_C64)
-    hipLaunchKernelGGL(residual_kernel<float2>, dim3((unsigned)blocks), dim3(kResThreads), 0, s, a, per, quads, bpr);
-  else
-    hipLaunchKernelGGL(residual_kernel<double2>, dim3((unsigned)blocks), dim3(kResThreads), 0, s, a, per, quads, bpr);
+  if (blocks > kFusedBlocks) a.counter = nullptr;
+  const dim3 g((unsigned)blocks);
+  if (a.dim == 2) {
+    if (a.r_kind == ST_C64)
+      hipLaunchKernelGGL(residual2d_kernel<float2>, g, dim3(kResThreads), 0, s, a, xt, bpr, strip);
+    else
+      hipLaunchKernelGGL(residual2d_kernel<double2>, g, dim3(kResThreads), 0, s, a, xt, bpr, strip);
+  } else {
+    if (a.r_kind == ST_C64)
+      hipLaunchKernelGGL(residual3d_kernel<float2>, g, dim3(k3Threads), 0, s, a, xt, yt, bpr, strip);
+    else
+      hipLaunchKernelGGL(residual3d_kernel<double2>, g, dim3(k3Threads), 0, s, a, xt, yt, bpr, strip);
+  }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(norm_finish_kernel, dim3((unsigned)a.nb), dim3(kFinThreads), 0, s, a.scratch, bpr, a.norms, a.skip);
+  if (e != hipSuccess || a.counter) return e;
+  hipLaunchKernelGGL(norm_finish_kernel, dim3((unsigned)a.nb), dim3(kFinThreads), 0, s, a.scratch, bpr, a.norms,
+                     a.skip);
+  e = hipGetLastError();
+  if (e != hipSuccess || !a.check.c) return e;
+  hipLaunchKernelGGL(ir_check_kernel, dim3(1), dim3(1), 0, s, (const double*)a.norms, a.nb, a.check, a.skip);
   return hipGetLastError();
 }
 
