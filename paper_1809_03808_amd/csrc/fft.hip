@@ -201,17 +201,31 @@ template <typename C> constexpr int tile_w(int L) {
 // tuner: 64 KB (16 columns, 128-byte row segments) with the same 1024
 // threads, so that two blocks share a compute unit and one block's loads
 // overlap the other's LDS stages.  WO = 0 is the default tile.
-template <int L, typename C, int WO> constexpr int tile_w_of() { return WO ? WO : tile_w<C>(L); }
-template <int L, typename C, int WO> constexpr int min_waves_of() { return WO ? 8 : 1; }
+//
+// A third, narrow tile (WO = -1) for launches that would have fewer blocks than
+// the device has compute units: 8 values per thread in blocks of 64 to 256
+// threads, so a quarter to a sixteenth of the columns per block (row segments of
+// at least 16 bytes).  The short segments cost bandwidth, which a launch of that
+// size does not use: the 1024-point convolution of 513 x 200 x 4 complex64 took
+// 24 us in 52 blocks of 16 columns and in 200 of 4, 14 us in 400 of 2.
+constexpr int narrow_threads(int L) { return L >= 512 ? 256 : (L >= 256 ? 128 : 64); }
+template <typename C> constexpr int narrow_w(int L) {
+  return pow2_floor(std::max(narrow_threads(L) * 8 / L, 16 / (int)sizeof(C)));
+}
+template <int L, typename C, int WO> constexpr int tile_w_of() {
+  return WO < 0 ? narrow_w<C>(L) : (WO ? WO : tile_w<C>(L));
+}
+template <int L, int WO> constexpr int threads_for() { return WO < 0 ? narrow_threads(L) : threads_of(L); }
+template <int L, typename C, int WO> constexpr int min_waves_of() { return WO > 0 ? 8 : 1; }
 
 // One Stockham stage of radix R with Ns points already combined.  Thread
-// tid of NT = threads_of(L) owns butterflies t = tid + q*NT, t -> (j = t / W,
+// tid of NT owns butterflies t = tid + q*NT, t -> (j = t / W,
 // w = t % W); since W divides NT, w = tid % W for every q.  All reads of a
 // stage precede the barrier and all writes follow it, so the stage works in
 // place in LDS.  The first stage reads global memory, the last writes it
 // (with the four-step twiddle, the per-mode scale and the optional
 // accumulation).
-template <int L, int W, int R, int Ns, bool FIRST, bool LAST, typename C, bool GIN = true, bool GOUT = true,
+template <int L, int W, int NT, int R, int Ns, bool FIRST, bool LAST, typename C, bool GIN = true, bool GOUT = true,
           bool REG = false>
 __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out, int64_t o, int64_t i0,
                              int64_t oq, int64_t orr, int64_t a4, const C* vin, int tid) {
@@ -219,7 +233,6 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
   constexpr bool STOREG = LAST && GOUT;   // this stage writes global memory
   constexpr int LR = L / R;
   constexpr int NBF = LR * W;
-  constexpr int NT = threads_of(L);
   static_assert(NT % W == 0 && L * W * (int)sizeof(C) <= 160 * 1024, "tile does not fit the thread block or LDS");
   constexpr int NB = (NBF + NT - 1) / NT;
   const int w = tid % W;
@@ -307,22 +320,23 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
   if constexpr (!STOREG) __syncthreads();
 }
 
-template <int L, int W, int S, int Ns, typename C, bool GIN = true, bool GOUT = true, bool REG = false>
+template <int L, int W, int NT, int S, int Ns, typename C, bool GIN = true, bool GOUT = true, bool REG = false>
 __device__ inline void stages(const PassDev& p, C* sm, const void* in, void* out, int64_t o, int64_t i0,
                               int64_t oq, int64_t orr, int64_t a4, const C* vin = nullptr,
                               int tid = (int)threadIdx.x) {
   if constexpr (S < nstages(L)) {
     constexpr int R = radix_of(L, S);
-    stage<L, W, R, Ns, S == 0, S == nstages(L) - 1, C, GIN, GOUT, REG>(p, sm, in, out, o, i0, oq, orr, a4, vin,
-                                                                          tid);
-    stages<L, W, S + 1, Ns * R, C, GIN, GOUT, REG>(p, sm, in, out, o, i0, oq, orr, a4, vin, tid);
+    stage<L, W, NT, R, Ns, S == 0, S == nstages(L) - 1, C, GIN, GOUT, REG>(p, sm, in, out, o, i0, oq, orr, a4, vin,
+                                                                           tid);
+    stages<L, W, NT, S + 1, Ns * R, C, GIN, GOUT, REG>(p, sm, in, out, o, i0, oq, orr, a4, vin, tid);
   }
 }
 
 template <int L, typename C, int WO = 0>
-__global__ __launch_bounds__(threads_of(L), (min_waves_of<L, C, WO>())) void fft_pass_kernel(PassDev p, const void* in,
-                                                                                            void* out) {
-  constexpr int W = tile_w_of<L, C, WO>();
+__global__ __launch_bounds__((threads_for<L, WO>()), (min_waves_of<L, C, WO>())) void fft_pass_kernel(PassDev p,
+                                                                                                     const void* in,
+                                                                                                     void* out) {
+  constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
   __shared__ C sm[nstages(L) > 1 ? L * W : 1];
   if (p.skip && *p.skip) return;
   const int64_t blk = blockIdx.x;
@@ -330,7 +344,7 @@ __global__ __launch_bounds__(threads_of(L), (min_waves_of<L, C, WO>())) void fft
   const int64_t i0 = (blk - o * p.ntile) * W;
   const int64_t oq = o / p.od, orr = o - oq * p.od;
   const int64_t a4 = p.tw4 ? (i0 + (int64_t)(threadIdx.x % W)) / p.tw4_S : 0;
-  stages<L, W, 0, 1, C>(p, sm, in, out, o, i0, oq, orr, a4);
+  stages<L, W, NT, 0, 1, C>(p, sm, in, out, o, i0, oq, orr, a4);
 }
 
 // Streaming form of the 512-point pass (the plan's tile choice 2): one
@@ -428,9 +442,9 @@ __global__ __launch_bounds__(threads_of(L), 1) void fft_stream_kernel(PassDev p0
     asm volatile("" : "+s"(osk), "+v"(tl));
     p.out_sk = osk;
     // first stage from the registers into LDS, then the next tile's loads
-    stage<L, W, R0, 1, true, nstages(L) == 1, C, true, true, true>(p, sm, in, out, o, i0, o, 0, 0, v, tl);
+    stage<L, W, NT, R0, 1, true, nstages(L) == 1, C, true, true, true>(p, sm, in, out, o, i0, o, 0, 0, v, tl);
     if (tile + G < ntot) ok = fetch(tile + G);
-    stages<L, W, 1, R0, C, true, true, true>(p, sm, in, out, o, i0, o, 0, 0, v, tl);
+    stages<L, W, NT, 1, R0, C, true, true, true>(p, sm, in, out, o, i0, o, 0, 0, v, tl);
   }
 }
 
@@ -439,18 +453,18 @@ __global__ __launch_bounds__(threads_of(L), 1) void fft_stream_kernel(PassDev p0
 // conjugating epilogue: conj(DFT(conj(X))) is the unscaled inverse DFT.
 // With L the whole convolution length and the chirps folded into the first
 // load and the last store, it is the complete transform in one pass.
-template <int L, typename C>
-__global__ __launch_bounds__(threads_of(L)) void conv_pass_kernel(PassDev p, const void* in, void* out) {
-  constexpr int W = tile_w<C>(L);
+template <int L, typename C, int WO = 0>
+__global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassDev p, const void* in, void* out) {
+  constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
   __shared__ C sm[L * W];
   if (p.skip && *p.skip) return;
   const int64_t blk = blockIdx.x;
   const int64_t o = blk / p.ntile;
   const int64_t i0 = (blk - o * p.ntile) * W;
   const int64_t oq = o / p.od, orr = o - oq * p.od;
-  stages<L, W, 0, 1, C, true, false>(p, sm, in, out, o, i0, oq, orr, 0);
+  stages<L, W, NT, 0, 1, C, true, false>(p, sm, in, out, o, i0, oq, orr, 0);
   const C* hk = reinterpret_cast<const C*>(p.cmode);
-  for (int e = threadIdx.x; e < L * W; e += threads_of(L)) {
+  for (int e = threadIdx.x; e < L * W; e += NT) {
     const int d = e / W;
     C y = cmul(sm[e], hk[orr + p.od * d]);
     y.y = -y.y;
@@ -460,18 +474,43 @@ __global__ __launch_bounds__(threads_of(L)) void conv_pass_kernel(PassDev p, con
   PassDev q = p;
   q.cmode = nullptr;
   q.cin = nullptr;
-  stages<L, W, 0, 1, C, false, true>(q, sm, in, out, o, i0, oq, orr, 0);
+  stages<L, W, NT, 0, 1, C, false, true>(q, sm, in, out, o, i0, oq, orr, 0);
 }
 
-template <int L, typename C>
+// Compute units of the current device.  (Cached per device; threads that race
+// on the first query store the same value.)
+int compute_units() {
+  static std::atomic<int> cu[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int n = cu[dev].load(std::memory_order_relaxed);
+  if (n <= 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    cu[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
+// Would a launch of the default tile leave compute units without a block, and
+// does the narrow tile give more blocks?
+template <int L, typename C> bool narrow_launch(const PassDev& p, int64_t O) {
+  constexpr int W = tile_w<C>(L), WN = narrow_w<C>(L);
+  return WN < W && p.I > WN && O * ((p.I + W - 1) / W) < compute_units();
+}
+
+template <int L, typename C, int WO = 0>
 hipError_t launch_conv_L(const PassDev& p, int64_t O, const void* in, void* out, hipStream_t s) {
-  constexpr int W = tile_w<C>(L);
+  if constexpr (WO == 0 && L >= 64) {
+    if (narrow_launch<L, C>(p, O)) return launch_conv_L<L, C, -1>(p, O, in, out, s);
+  }
+  constexpr int W = tile_w_of<L, C, WO>();
   PassDev q = p;
   q.ntile = (p.I + W - 1) / W;
   const int64_t blocks = O * q.ntile;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((conv_pass_kernel<L, C>), dim3((unsigned)blocks), dim3(threads_of(L)), 0, s, q, in, out);
+  hipLaunchKernelGGL((conv_pass_kernel<L, C, WO>), dim3((unsigned)blocks), dim3((threads_for<L, WO>())), 0, s, q, in,
+                     out);
   return hipGetLastError();
 }
 
@@ -492,41 +531,33 @@ hipError_t launch_conv_typed(int L, const PassDev& p, int64_t O, const void* in,
     case 256: return launch_conv_L<256, C>(p, O, in, out, s);
     case 512: return launch_conv_L<512, C>(p, O, in, out, s);
     // whole chirp-z convolutions in one pass (the plan's choice per axis)
+    case 144: return launch_conv_L<144, C>(p, O, in, out, s);
+    case 288: return launch_conv_L<288, C>(p, O, in, out, s);
     case 576: return launch_conv_L<576, C>(p, O, in, out, s);
     case 1152: return launch_conv_L<1152, C>(p, O, in, out, s);
     case 2304: return launch_conv_L<2304, C>(p, O, in, out, s);
     case 4608: return launch_conv_L<4608, C>(p, O, in, out, s);
     case 1024: return launch_conv_L<1024, C>(p, O, in, out, s);
     case 2048: return launch_conv_L<2048, C>(p, O, in, out, s);
+    case 4096: return launch_conv_L<4096, C>(p, O, in, out, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int L, typename C, int WO = 0>
 hipError_t launch_L(const PassDev& p, int64_t O, const void* in, void* out, hipStream_t s) {
+  if constexpr (WO == 0 && L >= 64) {
+    if (narrow_launch<L, C>(p, O)) return launch_L<L, C, -1>(p, O, in, out, s);
+  }
   constexpr int W = tile_w_of<L, C, WO>();
   PassDev q = p;
   q.ntile = (p.I + W - 1) / W;
   const int64_t blocks = O * q.ntile;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fft_pass_kernel<L, C, WO>), dim3((unsigned)blocks), dim3(threads_of(L)), 0, s, q, in, out);
+  hipLaunchKernelGGL((fft_pass_kernel<L, C, WO>), dim3((unsigned)blocks), dim3((threads_for<L, WO>())), 0, s, q, in,
+                     out);
   return hipGetLastError();
-}
-
-// Compute units of the current device, for the streaming pass's grid.
-// (Cached per device; threads that race on the first query store the same
-// value.)
-int compute_units() {
-  static std::atomic<int> cu[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int n = cu[dev].load(std::memory_order_relaxed);
-  if (n <= 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cu[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
 }
 
 template <int L, typename C, typename TIN, int W>

@@ -88,8 +88,8 @@ struct PAxis {
   BDiff bd;
   int na = 0, nbp = 0;  // FFT split n = na * nbp (nbp = first pass length); na = 1 -> one pass
   // Bluestein (chirp-z) transform for lengths that are not powers of two:
-  // convolution length M >= 2n - 1 (a power of two, or 9 * 2^j) split as
-  // Mna * Mnbp (Mna = 9 in the second case).
+  // convolution length M >= 2n - 2 (a power of two, or 9 * 2^j) split as
+  // Mna * Mnbp (setup_bluestein).
   int blue = 0, M = 0, Mna = 0, Mnbp = 0;
   int onepass = 0;  // the whole chirp-z convolution in one pass (tuned)
   DevMem btab;
@@ -358,22 +358,28 @@ void pow2_split(int L, int* na, int* nb) {
 // Bluestein tables of a periodised axis of length n (not a power of two):
 // chirp w_s[j] = e^{s pi i (j^2 mod 2n)/n} and the length-M forward DFT of the
 // kernel b_s[m] = e^{-s pi i m^2/n} (m in (-n, n), wrapped modulo M), s = -1, +1.
-// The convolution length M >= 2n - 1 is the smaller of the next power of two
-// and 9 * 2^j >= 576, split as nb (the passes that carry the chirps, a power
-// of two, 64 <= nb <= 512) times na = 9 * 2^k <= 72 (the convolution pass):
-// for the paper's n = 2^k + 1 that is 2.25 n instead of 4 n.
+// The convolution length M >= 2n - 2 is the smaller of the next power of two
+// and 9 * 2^j >= 72.  2n - 2 points suffice where a convolution of n points
+// with a kernel of 2n - 1 would take 2n - 1, because the kernel is even: its
+// first and last entries m = -(n - 1) and n - 1, which coincide modulo 2n - 2,
+// are equal.  So the paper's n = 2^k + 1 take M = 2^(k+1), twice the length of
+// the axis, where M >= 2n - 1 needs 2.25 to 4 times it.  Power-of-two lengths
+// above 512 split into two factors; 9 * 2^j >= 576 into nb (the passes that
+// carry the chirps, a power of two, 64 <= nb <= 512) times na = 9 * 2^k <= 72
+// (the convolution pass); 72, 144 and 288 only run as one pass.
 int setup_bluestein(PAxis& a) {
   const int n = a.n;
   int M = 1;
-  while (M < 2 * n - 1) M <<= 1;
+  while (M < 2 * n - 2) M <<= 1;
   if (M > 512 * 512) return HELM_EUNSUPPORTED;
-  int M9 = 9;
-  while (M9 < 2 * n - 1) M9 <<= 1;
+  int M9 = 72;
+  while (M9 < 2 * n - 2) M9 <<= 1;
   a.blue = 1;
-  if (M9 < M && M9 >= 576 && M9 <= 72 * 512) {
+  if (M9 < M && M9 <= 72 * 512) {
     M = M9;
-    a.Mnbp = M9 <= 4608 ? 64 : M9 / 72;
+    a.Mnbp = M9 < 576 ? 1 : (M9 <= 4608 ? 64 : M9 / 72);
     a.Mna = M9 / a.Mnbp;
+    a.onepass = a.Mnbp == 1;
   } else {
     pow2_split(M, &a.Mna, &a.Mnbp);
   }
@@ -455,7 +461,7 @@ int prepare_roots(helm_plan* p) {
       if (a.na > 1) lens.insert(lens.end(), {a.na, a.nbp});
     } else {
       lens = {a.M};
-      if (a.Mna > 1) lens.insert(lens.end(), {a.Mna, a.Mnbp});
+      if (a.Mna > 1 && a.Mnbp > 1) lens.insert(lens.end(), {a.Mna, a.Mnbp});
     }
     for (int L : lens)
       for (int sign : {-1, +1})
@@ -562,8 +568,8 @@ int run_pow2(helm_plan* p, int L, int na, int nb, int sign, bool fp32, const voi
 // Forward: sign -1 and per-mode scale 1/mu (if scale), inverse: sign +1, 1/n.
 // Lengths that are not powers of two use Bluestein's chirp-z algorithm:
 // jk = (j^2 + k^2 - (k - j)^2)/2 turns the DFT into a convolution with the
-// chirp kernel, evaluated with transforms of length M >= 2n - 1 (a power of
-// two, or 9 * 2^j as a length-2^j pass and a length-9 convolution pass).
+// chirp kernel, evaluated with transforms of length M >= 2n - 2 (a power of
+// two, or 9 * 2^j as a length-2^j pass and a convolution pass).
 // The chirp multiplications are folded into the first load and the last
 // store, and the convolution's middle (forward pass, kernel product, inverse
 // pass) is one kernel, so a transform costs n + M + 2M + M + n element moves
@@ -2183,7 +2189,7 @@ int tune_fft_tile(helm_plan* p) {
 // never reach memory).  Timed per such axis on a volume of the plan's shape
 // and precision; cached as "chirp<axis>=".
 bool onepass_length(int M) {
-  return M == 576 || M == 1152 || M == 2304 || M == 4608 || M == 1024 || M == 2048 ||
+  return M == 72 || M == 144 || M == 288 || M == 576 || M == 1152 || M == 2304 || M == 4608 || M == 1024 || M == 2048 || M == 4096 ||
          (M >= 2 && M <= 512 && !(M & (M - 1)));
 }
 
@@ -2196,7 +2202,7 @@ int tune_chirp(helm_plan* p) {
   for (int j = 0; j < p->dim; ++j) N *= p->grid[j];
   for (int j = 0; j < p->nper; ++j) {
     PAxis& A = p->ax[j];
-    if (!A.blue || !onepass_length(A.M)) continue;
+    if (!A.blue || A.Mnbp == 1 || !onepass_length(A.M)) continue;  // (Mnbp = 1: one pass is the only form)
     char field[16];
     std::snprintf(field, sizeof field, "chirp%d=", j);
     int cached = -1;
