@@ -75,24 +75,25 @@ extern "C" {
 #define HELM_DENSE_MAX 1024
 
 /* Evaluation of the boundary steps in 3D (helm_options.boundary; 2D always
- * uses line sweeps).  Step 2 of the method (eqs. (step2-1)-(step2-3)) maps two
- * boundary vectors to w_k = sum_k' sum_j V^b[k,j] V^b[k',j] T_j^{-1} r_k', a
- * linear map that depends on the operator only:
- *   LINES   sweep the N/n_3 line systems for it in every solve (the inner
- *           Step 2 of the outer Steps 1 and 3, and the whole outer Step 2);
- *   TABLES  build that map once at setup as dense n_3 x n_3 blocks (per outer
- *           mode for the inner Step 2, per inner absorbing mode for the outer
- *           Step 2, the latter after the dense inner eigenvector transform of
- *           the two boundary planes) and apply it as a batched matrix product:
- *           5 of the 9 line sweeps of a 3D solve become products with
- *           64 n_3^2 (n_1 + n_2) bytes of tables
- *           (complex128; half that, complex64, for HELM_PREC_MIXED plans);
+ * uses line sweeps).  The boundary steps of the method (eqs. (step2-1)-(step3term)
+ * of the outer level and of every inner solve) are linear maps of boundary
+ * vectors that depend on the operator only:
+ *   LINES   sweep the N/n_3 line systems for them in every solve (nine sweeps
+ *           of the whole grid);
+ *   TABLES  evaluate them in the eigenbasis of the last axis, where every line
+ *           matrix is diagonal, from tables built once at setup (the
+ *           eigenvectors of the last axis and the Step-2 maps of every mode,
+ *           16 (2 n_3^2 + 2 n_2^2 + 3 (n_1 + n_2) n_3) bytes): three sweeps of the
+ *           grid and products of boundary vectors remain.  A last axis without
+ *           a well-conditioned eigenbasis (coinciding eigenvalues: an axis with
+ *           both faces absorbing at about 3 points per wavelength and below)
+ *           takes LINES;
  *   AUTO    build the tables when they fit the memory budget (at most 32 GiB
  *           and a quarter of the free device memory) and use them for solves
  *           of at least as many right-hand sides as the plan measured them to
  *           pay for (timed at setup with 1 and 16 right-hand sides; cached in
  *           tune_cache when set).
- * Both give A^{-1} f up to rounding. */
+ * Both give A^{-1} f up to rounding; the report says which one ran. */
 #define HELM_BOUNDARY_AUTO   0
 #define HELM_BOUNDARY_LINES  1
 #define HELM_BOUNDARY_TABLES 2

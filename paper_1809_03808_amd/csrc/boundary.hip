@@ -19,20 +19,6 @@ namespace {
 
 constexpr int kMidThreads = 256;
 
-__global__ __launch_bounds__(kMidThreads) void sum_partials_kernel(const double2* __restrict__ part,
-                                                                   int64_t ngroups, int ntiles, int nL,
-                                                                   double2* __restrict__ out, const int* skip) {
-  if (skip && *skip) return;
-  const int64_t i = (int64_t)blockIdx.x * kMidThreads + threadIdx.x;
-  const int64_t per = 2 * (int64_t)nL;
-  if (i >= ngroups * per) return;
-  const int64_t g = i / per, r = i - g * per;
-  const double2* p = part + g * ntiles * per + r;
-  double2 s = make_double2(0, 0);
-  for (int t = 0; t < ntiles; ++t) s = cadd(s, p[t * per]);
-  out[i] = s;
-}
-
 // One block per (group, 30 columns): NT / 32 tile slices x 32 columns (the 30
 // outputs plus a halo of one on each side) sum the partials in parallel, the
 // slices are combined in LDS in a fixed order, then the 2x2 block operator is
@@ -159,16 +145,6 @@ __global__ __launch_bounds__(kMidThreads) void outer_mid_kernel(OuterMidArgs a) 
 }
 
 }  // namespace
-
-hipError_t launch_sum_partials(const double2* part, int ngroups, int ntiles, int nL, double2* out,
-                               const int* skip, hipStream_t s) {
-  const int64_t n = (int64_t)ngroups * 2 * nL;
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + kMidThreads - 1) / kMidThreads;
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)blocks), dim3(kMidThreads), 0, s, part,
-                     (int64_t)ngroups, ntiles, nL, out, skip);
-  return hipGetLastError();
-}
 
 hipError_t launch_inner_mid(const InnerMidArgs& a, hipStream_t s) {
   const int ntx = (a.nL + kMidOut - 1) / kMidOut;

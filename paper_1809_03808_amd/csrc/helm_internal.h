@@ -174,10 +174,6 @@ struct LineArgs {
   int tile = 0;    // lines per workgroup tile
   int ntiles = 0;  // tiles along the reduced (or flattened) index
   const int* skip = nullptr;     // device flag: the launch does nothing while *skip != 0
-  // Unit right-hand sides (plan setup only): with no `in`, line (b, l, m) has
-  // the right-hand side e_b (b < nL), so that reductions of the solutions
-  // assemble columns of reduced inverses (the boundary operator tables).
-  int unit_rhs = 0;
   // Storing launches (red == 0): blocks take tiles of tile_l outer x tile_m
   // inner modes of one right-hand side (0: consecutive lines, `tile` each).
   int tile_l = 0, tile_m = 0;
@@ -193,30 +189,74 @@ void lines_geometry(int nL, int* P, int* c, int* NT);
 hipError_t launch_line_factors(const LineArgs& a, double2* piv, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Boundary operator tables (cap.hip): for every group g < G (an outer or an
-// inner mode), the reduced inverse of that group's line matrices acting on
-// two boundary vectors,
-//   out[b][g][k][x] = sum_{k' < 2} sum_{x' < nL} T_{k'}[g][x'][k][x] in[b][g][k'][x'],
-// with T_{k'} stored [G][nL (x')][2 (k)][nL (x)] (complex128, or complex64
-// when t_fp32) and the vectors addressed by b * _b + g * _g + k * _k + x
-// strides; accumulated in FP64.
+// 2x2 boundary difference of a periodised axis (B - A restricted to its two
+// end nodes): dK = (1/h)[[1 + i w h a_lo, -1], [-1, 1 + i w h a_hi]],
+// dM = (h/6)[[2, 1], [1, 2]].
 // ---------------------------------------------------------------------------
-struct CapArgs {
-  int nb = 0, G = 0, nL = 0;
-  const void* T0 = nullptr;
-  const void* T1 = nullptr;
-  int t_fp32 = 0;
+struct BDiff {
+  double2 dK[2][2];
+  double dM[2][2];
+};
+
+// ---------------------------------------------------------------------------
+// Boundary steps of a 3D solve in the eigenbasis of the last axis (modal.hip).
+// Boundary vectors are [nb][n][2][nL] (right-hand side, mode, end node,
+// component).
+// ---------------------------------------------------------------------------
+// Partial sums of two sets of groups: o[g][r] = sum_t p[g][t][r], t < nt, r < 2 nL.
+hipError_t launch_modal_gather(const double2* p0, int64_t g0, int nt0, double2* o0, const double2* p1, int64_t g1,
+                               int nt1, double2* o1, int nL, const int* skip, hipStream_t s);
+
+// Rows (b, g, k), g < n, times an nL x nL matrix Q:
+//   out[b ob + g og + k ok + x] = sum_i in[((b n + g) 2 + k) nL + i] Q[i][x]
+struct ModalRows {
+  int n = 0;
   const double2* in = nullptr;
-  int64_t in_b = 0, in_g = 0, in_k = 0;
-  double2* out = nullptr;
-  int64_t out_b = 0, out_g = 0, out_k = 0;
+  void* out = nullptr;
+  int out_c64 = 0;
+  int64_t ob = 0, og = 0, ok = 0;
+};
+hipError_t launch_modal_rows(const double2* Q, int nL, int nb, const ModalRows* sets, int nsets, const int* skip,
+                             hipStream_t s);
+
+// q = A (a + S A a) per (b, g, p): A = dK + (sO[g] + lam[p]) dM, S the
+// symmetric 2 x 2 table tab[g][00, 01, 11][p].
+struct ModalMid {
+  const double2* tab = nullptr;
+  const double2* sO = nullptr;
+  BDiff d;
+};
+hipError_t launch_modal_mid(const ModalMid& m, int nb, int nG, int nL, const double2* lam, const double2* in,
+                            double2* out, const int* skip, hipStream_t s);
+
+// Sums over the modes s < nS for every mode g < nG (modal_sum_kernel): X and
+// the result as boundary vectors over s and over g, sigma of (s, g) at
+// sig[s sS + g sG], followed by `mid` when it has a table.
+struct ModalSum {
+  int nb = 0, nS = 0, nG = 0, nL = 0;
+  const double2* sig = nullptr;
+  int64_t sS = 0, sG = 0;
+  const double2* lam = nullptr;    // eigenvalues of the last axis, and their
+  const double2* lamlo = nullptr;  // rounding errors
+  const double2* X = nullptr;
+  const double2* rho1 = nullptr;   // [nS]; rho_0 = 1/nS
+  const double2* gen0 = nullptr;   // [nG]
+  const double2* gen1 = nullptr;
+  const double2* add = nullptr;
+  double2* out = nullptr;          // may be `add`
+  ModalMid mid;
   const int* skip = nullptr;
 };
-hipError_t launch_cap_apply(const CapArgs& a, hipStream_t s);
-// dst[g][x'][k][x] = src[x'][g][k][x] (G groups, 2 nL rows), narrowed to
-// complex64 when fp32: the layout the line reductions produce -> the one the
-// products stream.
-hipError_t launch_cap_reorder(const double2* src, void* dst, int G, int nL, bool fp32, hipStream_t s);
+hipError_t launch_modal_sum(const ModalSum& a, hipStream_t s);
+
+// Plan setup: tab[g][00, 01, 11][p] = sum_s (v0 v0, v0 v1, v1 v1)[s] / (sig[s sS + g sG] + lam[p]);
+// M V of an axis and its transpose; a transpose; h times the squared column norms.
+hipError_t launch_modal_table(const double2* sig, int64_t sS, int64_t sG, int nS, int nG, int nL, const double2* lam,
+                              const double2* lamlo, const double2* v0, const double2* v1, double2* tab,
+                              hipStream_t s);
+hipError_t launch_mass_vec(const double2* V, int n, double h, double2* MV, double2* MVT, hipStream_t s);
+hipError_t launch_transpose(const double2* in, int n, double2* out, hipStream_t s);
+hipError_t launch_col_norms(const double2* V, int n, double h, double* nrm, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Dense eigenvector transforms on the matrix cores (dense.hip)
@@ -241,14 +281,6 @@ hipError_t launch_dense(const DenseArgs& a, bool fp32, hipStream_t s);
 // ---------------------------------------------------------------------------
 // Boundary kernels (boundary.hip)
 // ---------------------------------------------------------------------------
-// 2x2 boundary difference of a periodised axis (B - A restricted to its two
-// end nodes): dK = (1/h)[[1 + i w h a_lo, -1], [-1, 1 + i w h a_hi]],
-// dM = (h/6)[[2, 1], [1, 2]].
-struct BDiff {
-  double2 dK[2][2];
-  double dM[2][2];
-};
-
 // Inner boundary operator for every (b, l): with v = sum over tiles of
 // part[(b nO + l) ntiles + t][k][:] (+ vb_in[b][l][k][:] if add_vb),
 //   out[b][l][k][:] = sum_k' (dK - p_l dM)[k][k'] M_L v_k' + dM[k][k'] K_L v_k',
@@ -269,10 +301,6 @@ struct InnerMidArgs {
   const int* skip = nullptr;
 };
 hipError_t launch_inner_mid(const InnerMidArgs& a, hipStream_t s);
-
-// Sum partial planes: out[g][k][:] = sum_t part[g ntiles + t][k][:], g < ngroups.
-hipError_t launch_sum_partials(const double2* part, int ngroups, int ntiles, int nL,
-                               double2* out, const int* skip, hipStream_t s);
 
 // Outer boundary operator on physical (x2, x3) planes (3D):
 //   r[b][k] = sum_k' (dK1 - w^2 dM1)[k][k'] (M2 (x) M3) v_k' + dM1[k][k'] (K2 (x) M3 + M2 (x) K3) v_k'

@@ -269,7 +269,6 @@ struct LineDev {
   void* out;
   double2* part;
   const int* skip;
-  int unit_rhs;
 };
 
 struct RowCoef {
@@ -545,9 +544,8 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR && !PAD) ? 4 : 1) voi
       } else {
 #pragma unroll
         for (int jj = 0; jj < kCMax; ++jj) {
-          const int r = jj * 64 + lane, x = wx0 + r;
-          const bool one = a.unit_rhs && sv && x == (int)sb;
-          if (r < seg) S[stage_pos(si * seg + r)] = make_double2(one ? 1.0 : 0.0, 0);
+          const int r = jj * 64 + lane;
+          if (r < seg) S[stage_pos(si * seg + r)] = make_double2(0, 0);
         }
       }
       // Rank-2 terms.  Kernels of exact lines load the rows of a source in
@@ -642,7 +640,6 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR && !PAD) ? 4 : 1) voi
     if (XR && last && valid) {
       const int x = nL - 1;
       if (a.in) xrhs = to_d2(reinterpret_cast<const T*>(a.in)[loff + x]);
-      else if (a.unit_rhs && (int)b == x) xrhs = make_double2(1, 0);
       if (a.PO) {
         const T* po = reinterpret_cast<const T*>(a.PO) + (int64_t)(b * 2) * a.nI * nL + (int64_t)m * nL;
         xrhs = cfma(a.alpha0[l], to_d2(po[x]), xrhs);
@@ -944,7 +941,6 @@ LineDev make_dev(const LineArgs& a, int P, int c) {
   d.sTab = a.sTab;
   d.out = a.out; d.part = a.part;
   d.skip = a.skip;
-  d.unit_rhs = a.unit_rhs;
   d.tile = d.ntiles = d.iters = 0;
   d.tl = d.tm = 0;
   d.xcd = 0;

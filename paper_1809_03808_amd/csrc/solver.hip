@@ -143,18 +143,19 @@ struct helm_plan {
   // leaves it zero)
   helm::DevMem res_count;
   int dense = 0;  // 1: periodised axes use the dense eigenvector transforms
-  // Boundary operator tables (3D, helm_options.boundary): capW holds the
-  // inner Step-2 map of every outer periodic mode l (line family (B, A)),
-  // capH the outer Step-2 map of every inner absorbing mode m (family
-  // (A, A)); each as two blocks T_{k'}[g][x'][k][x] (cap.hip).  Solves of at
-  // least cap_min_nb right-hand sides use them (0: never).
-  helm::DevMem capW, capH;
-  const void *capW0 = nullptr, *capW1 = nullptr, *capH0 = nullptr, *capH1 = nullptr;
-  int cap_fp32 = 0;  // tables in complex64 (mixed-precision plans)
-  int cap_min_nb = 0;
+  // Boundary steps in the eigenbasis of the last axis (3D,
+  // helm_options.boundary; modal.hip): eigenvalues of the last axis and their
+  // rounding errors, M_3 V_3 and its transpose, the inner and outer Step-2
+  // tables, and the products of the x_2 eigenvectors with the DFT matrices
+  // that take the outer step from Fourier modes to eigenvectors and back.
+  // Solves of at least modal_min_nb right-hand sides use them (0: never).
+  helm::DevMem modal;
+  const double2 *mlam = nullptr, *mlamlo = nullptr, *mMV = nullptr, *mMVT = nullptr, *mS = nullptr, *mH = nullptr,
+                *mG1 = nullptr, *mG2 = nullptr;
+  int modal_min_nb = 0;
   int red_layout = 2;  // layout of the line reductions over the outer modes (2 or 3)
   int fft_small = 0;   // 512-point passes: 0 the 128 KB tile, 1 the 64 KB complex64 tile, 2 streaming (tuned)
-  double cap_ms[4] = {-1, -1, -1, -1};  // measured: lines at 1 and 16 RHS, tables at 1 and 16 RHS
+  double modal_ms[4] = {-1, -1, -1, -1};  // measured: lines at 1 and 16 RHS, tables at 1 and 16 RHS
   std::string tune_path;
   double tune_ms[2] = {-1.0, -1.0};  // measured FFT / dense solve times (AUTO)
   std::vector<double> h_norms;
@@ -241,7 +242,7 @@ int map_err(hipError_t e) {
 // Kernel slots of helm_kernel_stats.
 enum KSlot {
   K_FFT64 = 0, K_FFT32 = 1, K_LINES = 2, K_INNER_MID = 3, K_SUM = 4, K_OUTER_MID = 5, K_RESID = 6, K_DENSE = 7,
-  K_CAP = 8
+  K_MODAL = 8
 };
 
 // Launch through `fn` (returning hipError_t), bracketed by events if profiling.
@@ -839,34 +840,27 @@ struct InnerIO {
   const double2* seedA = nullptr;  // line matrices with the absorbing inner branch (S2)
   const double2* sigTB = nullptr;  // their sigma tables
   const double2* sigTA = nullptr;
-  bool capS2 = false;  // Step 2 from the plan's table capW instead of a line sweep
 };
 
-// Product of a boundary operator table with nb pairs of boundary vectors
-// (cap.hip), timed with the table bytes it streams.
-int cap_apply(helm_plan* p, const void* T0, const void* T1, int nb, int G, const double2* in,
-              int64_t in_b, int64_t in_g, int64_t in_k, double2* out, int64_t out_b, int64_t out_g, int64_t out_k,
-              hipStream_t st) {
-  CapArgs ca;
-  ca.nb = nb;
-  ca.G = G;
-  ca.nL = p->nL;
-  ca.T0 = T0;
-  ca.T1 = T1;
-  ca.t_fp32 = p->cap_fp32;
-  ca.in = in;
-  ca.in_b = in_b;
-  ca.in_g = in_g;
-  ca.in_k = in_k;
-  ca.out = out;
-  ca.out_b = out_b;
-  ca.out_g = out_g;
-  ca.out_k = out_k;
-  ca.skip = p->skip_cur;
-  const double by = 2.0 * G * (2.0 * p->nL) * p->nL * (p->cap_fp32 ? sizeof(float2) : sizeof(double2)) *
-                    ((nb + 15) / 16);
-  HCHK(timed(p, K_CAP, by, st, [&] { return launch_cap_apply(ca, st); }));
-  return HELM_OK;
+// Lines per block of a storing launch.  With rank-2 rows of the outer
+// direction, mode tiles of e outer x e/2 inner modes, e chosen so that a tile
+// has no more lines than the consecutive runs would have (the launch keeps its
+// number of blocks): the rank-2 rows of an inner mode are then re-read once
+// per tile instead of once per outer mode, and with the XCD-major tile order
+// the blocks resident on one XCD share the rows of their inner-mode tile in L2
+// (512^3 x 16 storing launch: fetch 52 GB untiled, 48 GB with 32 x 32 tiles,
+// 39 GB with 32 x 16).
+void store_tiles(const helm_plan* p, const Level& lv, bool outer_rows, LineArgs* a) {
+  tiles_for(p, 0, lv.nb, lv.nO, lv.nI, lv.nL, &a->tile, &a->ntiles);
+  if (!outer_rows) return;
+  int P, c, NT;
+  lines_geometry(lv.nL, &P, &c, &NT);
+  int e = 32;
+  while (e > 4 && (e * e / 2 > a->tile || e > lv.nO || e / 2 > lv.nI)) e /= 2;
+  if (e >= 8 && (e * e / 2) % (NT / P) == 0) {
+    a->tile_l = e;
+    a->tile_m = e / 2;
+  }
 }
 
 int inner_solve(helm_plan* p, const Level& lv, const InnerIO& io, hipStream_t st) {
@@ -926,31 +920,22 @@ int inner_solve(helm_plan* p, const Level& lv, const InnerIO& io, hipStream_t st
   HCHK(timed(p, K_INNER_MID, (double)lv.nb * lv.nO * 2 * lv.nL * sizeof(double2) * (nt + 2), st,
              [&] { return launch_inner_mid(m, st); }));
 
-  // S2: partial solution with the absorbing-boundary eigenvectors, as a
-  // line sweep or from the table of its map (one partial per (b, l))
-  if (io.capS2) {
-    const int64_t per = 2 * (int64_t)lv.nL, gs = (int64_t)lv.nO * per;
-    const int rc2 = cap_apply(p, p->capW0, p->capW1, lv.nb, lv.nO, p->PIb.as<double2>(), gs, per, lv.nL, part, gs,
-                              per, lv.nL, st);
-    if (rc2) return rc2;
-    m.ntiles = 1;
-  } else {
-    LineArgs s2 = base;
-    s2.sI = I.sigA;
-    s2.piv = io.seedA;
-    s2.sTab = io.sigTA;
-    s2.PI = p->PIb.p;  // complex128: the launch has no line storage
-    s2.r2_kind = ST_C128;
-    s2.beta0 = I.va0d;
-    s2.beta1 = I.va1d;
-    s2.red = 1;
-    s2.rho0 = I.va0d;
-    s2.rho1 = I.va1d;
-    s2.part = part;
-    s2.tile = tile;
-    s2.ntiles = nt;
-    HCHK(timed(p, K_LINES, 0.0, st, [&] { return launch_lines(s2, st); }));
-  }
+  // S2: partial solution with the absorbing-boundary eigenvectors
+  LineArgs s2 = base;
+  s2.sI = I.sigA;
+  s2.piv = io.seedA;
+  s2.sTab = io.sigTA;
+  s2.PI = p->PIb.p;  // complex128: the launch has no line storage
+  s2.r2_kind = ST_C128;
+  s2.beta0 = I.va0d;
+  s2.beta1 = I.va1d;
+  s2.red = 1;
+  s2.rho0 = I.va0d;
+  s2.rho1 = I.va1d;
+  s2.part = part;
+  s2.tile = tile;
+  s2.ntiles = nt;
+  HCHK(timed(p, K_LINES, 0.0, st, [&] { return launch_lines(s2, st); }));
 
   // the Step-3 launch reads these rows (PI) in its lines' storage type
   const int k3 = io.in ? io.in_kind : (io.out ? io.out_kind : ST_C128);
@@ -983,29 +968,9 @@ int inner_solve(helm_plan* p, const Level& lv, const InnerIO& io, hipStream_t st
     s3.tile = tl;
     s3.ntiles = ntl;
   } else {
-    int tl, ntl;
-    tiles_for(p, 0, lv.nb, lv.nO, lv.nI, lv.nL, &tl, &ntl);
     s3.out = io.out;
     s3.out_kind = io.out_kind;
-    s3.tile = tl;
-    s3.ntiles = ntl;
-    if (io.PO) {
-      // mode tiles of e outer x e/2 inner modes, e chosen so that a tile has
-      // no more lines than the consecutive runs would have (the launch keeps
-      // its number of blocks): the rank-2 rows of an inner mode are then
-      // re-read once per tile instead of once per outer mode, and with the
-      // XCD-major tile order the blocks resident on one XCD share the rows
-      // of their inner-mode tile in L2 (512^3 x 16 storing launch: fetch 52
-      // GB untiled, 48 GB with 32 x 32 tiles, 39 GB with 32 x 16)
-      int P, c, NT;
-      lines_geometry(lv.nL, &P, &c, &NT);
-      int e = 32;
-      while (e > 4 && (e * e / 2 > tl || e > lv.nO || e / 2 > lv.nI)) e /= 2;
-      if (e >= 8 && (e * e / 2) % (NT / P) == 0) {
-        s3.tile_l = e;
-        s3.tile_m = e / 2;
-      }
-    }
+    store_tiles(p, lv, io.PO != nullptr, &s3);
   }
   const double by3 = (io.in ? elems * esz_of(io.in_kind) : 0.0) + (io.out ? elems * esz_of(io.out_kind) : 0.0);
   HCHK(timed(p, K_LINES, by3, st, [&] { return launch_lines(s3, st); }));
@@ -1114,6 +1079,293 @@ int solve_dense(helm_plan* p, const void* x, int x_kind, double2* u, int accumul
   return dense_pass(p, n1, (int64_t)n2 * n3, nb, inv(A1), W0, T, u, ST_C128, accumulate, fp32, st);
 }
 
+// ---------------------------------------------------------------------------
+// Boundary steps of a 3D solve in the eigenbasis of the last axis (modal.hip)
+// ---------------------------------------------------------------------------
+struct ModalBufs {
+  const double2* part1 = nullptr;  // reductions over the inner modes [nb][n1][nt1][2][nL]
+  int nt1 = 1;
+  const double2* part2 = nullptr;  // reductions over the outer modes [nb][n2][nt2][2][nL]
+  int nt2 = 1;
+  bool first_done = false;         // q holds the summed part1 already
+  double2 *a1 = nullptr, *q = nullptr;                  // [nb][n1][2][nL]
+  double2 *v0 = nullptr, *v1 = nullptr, *v2 = nullptr;  // [nb][n2][2][nL]
+};
+
+ModalRows modal_rows_in(int n, int nL, const double2* in, double2* out) {
+  ModalRows r;
+  r.n = n;
+  r.in = in;
+  r.out = out;
+  r.ob = (int64_t)n * 2 * nL;
+  r.og = 2 * (int64_t)nL;
+  r.ok = nL;
+  return r;
+}
+
+int modal_rows(helm_plan* p, const double2* Q, int nb, const ModalRows* sets, int n, hipStream_t st) {
+  double rows = 0;
+  for (int i = 0; i < n; ++i) rows += 2.0 * nb * sets[i].n;
+  HCHK(timed(p, K_MODAL, rows * p->nL * 2 * sizeof(double2), st,
+             [&] { return launch_modal_rows(Q, p->nL, nb, sets, n, p->skip_cur, st); }));
+  return HELM_OK;
+}
+
+// From the two reductions of T^{-1} f^ (b.part1, b.part2) to the generated
+// rows of the storing sweep: PO into b.v0 ([nb][2][n2][nL]) and PI into b.a1
+// ([nb][n1][2][nL]), in complex64 when out_c64.
+//   a     = V^T M_3 (boundary values)
+//   q     = A_2 (a1 + S A_2 a1)                            inner Steps 1 and 2 of every outer mode
+//   V_h   = b + sum_l (generated rows q)                   outer Step 1: v_b in x_2 modes
+//   x_2 eigenvectors, A_1 (. + H A_1 .), back to x_2 modes outer Step 2: q of Step 3
+//   a1'   = a1 + sum_m (generated rows), q' = A_2 (a1' + S A_2 a1')   inner Steps of Step 3
+int modal_chain(helm_plan* p, const ModalBufs& b, int nb, bool out_c64, hipStream_t st) {
+  const PAxis& A1 = p->ax[0];
+  const PAxis& A2 = p->ax[1];
+  const int n1 = A1.n, n2 = A2.n, nL = p->nL;
+  const double e1 = 2.0 * nb * n1 * nL * sizeof(double2), e2 = 2.0 * nb * n2 * nL * sizeof(double2);
+  const double2 *s1 = b.part1, *s2 = b.part2;
+  if (b.first_done || b.nt1 > 1 || b.nt2 > 1) {
+    s1 = b.q;
+    s2 = b.v1;
+    HCHK(timed(p, K_MODAL, e1 * (b.nt1 + 1) + e2 * (b.nt2 + 1), st, [&] {
+      return launch_modal_gather(b.part1, b.first_done ? 0 : (int64_t)nb * n1, b.nt1, b.q, b.part2, (int64_t)nb * n2,
+                                 b.nt2, b.v1, nL, p->skip_cur, st);
+    }));
+  }
+  const ModalRows in[2] = {modal_rows_in(n1, nL, s1, b.a1), modal_rows_in(n2, nL, s2, b.v0)};
+  int rc = modal_rows(p, p->mMV, nb, in, 2, st);
+  if (rc) return rc;
+  ModalMid mi, mo;  // inner and outer boundary operators
+  mi.tab = p->mS;
+  mi.sO = A1.sigB;
+  mi.d = A2.bd;
+  mo.tab = p->mH;
+  mo.sO = A2.sigA;
+  mo.d = A1.bd;
+  HCHK(timed(p, K_MODAL, 2 * e1, st,
+             [&] { return launch_modal_mid(mi, nb, n1, nL, p->mlam, b.a1, b.q, p->skip_cur, st); }));
+  ModalSum s;
+  s.nb = nb;
+  s.nL = nL;
+  s.sig = p->sig[0];
+  s.lam = p->mlam;
+  s.lamlo = p->mlamlo;
+  s.skip = p->skip_cur;
+  s.nS = n1;
+  s.nG = n2;
+  s.sS = n2;
+  s.sG = 1;
+  s.X = b.q;
+  s.rho1 = A1.redB1;
+  s.gen0 = A2.genB0;
+  s.gen1 = A2.genB1;
+  s.add = b.v0;
+  s.out = b.v0;
+  HCHK(timed(p, K_MODAL, e1 + 2 * e2, st, [&] { return launch_modal_sum(s, st); }));
+  rc = dense_pass(p, n2, 2 * (int64_t)nL, nb, p->mG1, b.v0, ST_C128, b.v1, ST_C128, 0, false, st);
+  if (rc) return rc;
+  HCHK(timed(p, K_MODAL, 2 * e2, st,
+             [&] { return launch_modal_mid(mo, nb, n2, nL, p->mlam, b.v1, b.v1, p->skip_cur, st); }));
+  rc = dense_pass(p, n2, 2 * (int64_t)nL, nb, p->mG2, b.v1, ST_C128, b.v2, ST_C128, 0, false, st);
+  if (rc) return rc;
+  s.nS = n2;
+  s.nG = n1;
+  s.sS = 1;
+  s.sG = n2;
+  s.X = b.v2;
+  s.rho1 = A2.redB1;
+  s.gen0 = A1.genB0;
+  s.gen1 = A1.genB1;
+  s.add = b.a1;
+  s.out = b.q;
+  s.mid = mi;
+  HCHK(timed(p, K_MODAL, 2 * e1 + e2, st, [&] { return launch_modal_sum(s, st); }));
+  ModalRows out[2] = {modal_rows_in(n2, nL, b.v2, b.v0), modal_rows_in(n1, nL, b.q, b.a1)};
+  out[0].og = nL;
+  out[0].ok = (int64_t)n2 * nL;
+  out[0].out_c64 = out[1].out_c64 = out_c64;
+  return modal_rows(p, p->mMVT, nb, out, 2, st);
+}
+
+// The line work of a 3D solve with the boundary steps in the eigenbasis: two
+// reducing sweeps of f^ (W0), the chain above, and the storing sweep.
+int solve_modal(helm_plan* p, const Level& lv, int kind, hipStream_t st) {
+  const PAxis& A1 = p->ax[0];
+  const PAxis& A2 = *lv.inner;
+  LineArgs base;
+  base.skip = p->skip_cur;
+  base.nb = lv.nb;
+  base.nO = lv.nO;
+  base.nI = lv.nI;
+  base.nL = lv.nL;
+  base.hL = p->hL;
+  base.kLo = p->kLo;
+  base.kHi = p->kHi;
+  base.piv = p->seed[0];
+  base.sTab = p->sig[0];
+  base.in = p->W0.p;
+  base.in_kind = kind;
+  base.r2_kind = kind;
+  const double elems = (double)lv.nb * lv.nO * lv.nI * lv.nL;
+  ModalBufs b;
+  b.a1 = p->VB.as<double2>();
+  b.q = p->PIb.as<double2>();
+  b.v0 = p->P0.as<double2>();
+  b.v1 = p->P1.as<double2>();
+  b.v2 = p->P2.as<double2>();
+  LineArgs r1 = base;
+  r1.red = 1;
+  r1.rho0 = A2.redB0;
+  r1.rho1 = A2.redB1;
+  r1.part = p->part.as<double2>();
+  tiles_for(p, 1, lv.nb, lv.nO, lv.nI, lv.nL, &r1.tile, &r1.ntiles);
+  HCHK(timed(p, K_LINES, elems * esz_of(kind), st, [&] { return launch_lines(r1, st); }));
+  b.part1 = r1.part;
+  b.nt1 = r1.ntiles;
+  LineArgs r2 = base;
+  r2.red = red_l_mode(p);
+  r2.rho0 = A1.redB0;
+  r2.rho1 = A1.redB1;
+  tiles_for(p, 2, lv.nb, lv.nO, lv.nI, lv.nL, &r2.tile, &r2.ntiles);
+  // its partial sums into the idle transform buffer, or where they do not fit
+  // (few outer modes) over the first ones once those are summed
+  r2.part = p->W1.as<double2>();
+  if ((size_t)lv.nb * lv.nI * r2.ntiles * 2 * lv.nL * sizeof(double2) > p->W1.bytes) {
+    HCHK(timed(p, K_MODAL, 0.0, st, [&] {
+      return launch_modal_gather(b.part1, (int64_t)lv.nb * lv.nO, b.nt1, b.q, nullptr, 0, 1, nullptr, lv.nL,
+                                 p->skip_cur, st);
+    }));
+    b.first_done = true;
+    r2.part = r1.part;
+  }
+  HCHK(timed(p, K_LINES, elems * esz_of(kind), st, [&] { return launch_lines(r2, st); }));
+  b.part2 = r2.part;
+  b.nt2 = r2.ntiles;
+  const int rc = modal_chain(p, b, lv.nb, kind == ST_C64, st);
+  if (rc) return rc;
+  LineArgs s3 = base;
+  s3.PO = b.v0;
+  s3.alpha0 = A1.genB0;
+  s3.alpha1 = A1.genB1;
+  s3.PI = b.a1;
+  s3.beta0 = A2.genB0;
+  s3.beta1 = A2.genB1;
+  s3.out = p->W0.p;
+  s3.out_kind = kind;
+  store_tiles(p, lv, true, &s3);
+  HCHK(timed(p, K_LINES, 2 * elems * esz_of(kind), st, [&] { return launch_lines(s3, st); }));
+  return HELM_OK;
+}
+
+// Do solves of nb right-hand sides take the boundary steps in the eigenbasis?
+bool boundary_modal(const helm_plan* p, int nb) { return p->modal_min_nb > 0 && nb >= p->modal_min_nb; }
+
+// The line work of a 3D solve by line sweeps alone: the three outer steps,
+// each block solve of them the three inner steps.
+int solve_lines(helm_plan* p, const Level& lv, int T, hipStream_t st) {
+  const PAxis& A1 = p->ax[0];
+  const PAxis& A2 = *lv.inner;
+  const int nb = lv.nb, n2 = lv.nI, n3 = lv.nL;
+  const int64_t plane = (int64_t)n2 * n3;
+  const double w2 = lv.w2;
+  void* W0 = p->W0.p;
+  int rc;
+  double2* Vh = p->P0.as<double2>();  // [nb][2][n2][n3] scratch planes
+  double2* Vp = p->P1.as<double2>();
+  double2* Wp = p->P2.as<double2>();
+  double2* Rh = p->P3.as<double2>();
+  // Outer step 1: v_b.
+  {
+    InnerIO io;
+    io.sO = A1.sigB;
+    io.seedB = p->seed[0];
+    io.seedA = p->seed[1];
+    io.sigTB = p->sig[0];
+    io.sigTA = p->sig[1];
+    io.in = W0;
+    io.in_kind = T;
+    io.rhoL0 = A1.redB0;
+    io.rhoL1 = A1.redB1;
+    rc = inner_solve(p, lv, io, st);
+    if (rc) return rc;
+    rc = sum_to_planes(p, lv, Vh, st);
+    if (rc) return rc;
+    rc = run_fft(p, A2, +1, false, Vh, ST_C128, Vp, ST_C128, (int64_t)nb * 2, n3, nullptr, 1.0 / n2, 0,
+                 Wp, ST_C128, st);
+    if (rc) return rc;
+  }
+  // Outer step 2: r = C_1 v_b, w_b.
+  {
+    OuterMidArgs om;
+    om.skip = p->skip_cur;
+    om.nb = nb;
+    om.n2 = n2;
+    om.n3 = n3;
+    om.a = Vp;
+    om.c = nullptr;
+    om.r = Wp;
+    om.d1 = A1.bd;
+    om.w2 = w2;
+    om.h2 = A2.h;
+    om.h3 = p->hL;
+    om.k2Lo = corner_h(A2.glo, A2.h);
+    om.k2Hi = corner_h(A2.ghi, A2.h);
+    om.k3Lo = p->kLo;
+    om.k3Hi = p->kHi;
+    HCHK(timed(p, K_OUTER_MID, (double)nb * 2 * plane * sizeof(double2) * 3, st, [&] { return launch_outer_mid(om, st); }));
+    rc = run_fft(p, A2, -1, false, Wp, ST_C128, Rh, ST_C128, (int64_t)nb * 2, n3, A2.invmu, 1.0, 0, Vh,
+                 ST_C128, st);
+    if (rc) return rc;
+    InnerIO io;
+    io.sO = A1.sigA;
+    io.seedB = p->seed[2];
+    io.seedA = p->seed[3];
+    io.sigTB = p->sig[2];
+    io.sigTA = p->sig[3];
+    io.PO = Rh;
+    io.alpha0 = A1.va0d;
+    io.alpha1 = A1.va1d;
+    io.rhoL0 = A1.va0d;
+    io.rhoL1 = A1.va1d;
+    rc = inner_solve(p, lv, io, st);
+    if (rc) return rc;
+    rc = sum_to_planes(p, lv, Vh, st);
+    if (rc) return rc;
+    rc = run_fft(p, A2, +1, false, Vh, ST_C128, Wp, ST_C128, (int64_t)nb * 2, n3, nullptr, 1.0 / n2, 0,
+                 Rh, ST_C128, st);
+    if (rc) return rc;
+    // q = C_1 (v_b + w_b), transformed along x_2 and scaled by 1/mu_2; stored
+    // in the lines' storage type, as the rank-2 rows of the Step-3 lines
+    om.a = Vp;
+    om.c = Wp;
+    om.r = Vh;
+    HCHK(timed(p, K_OUTER_MID, (double)nb * 2 * plane * sizeof(double2) * 3, st, [&] { return launch_outer_mid(om, st); }));
+    rc = run_fft(p, A2, -1, false, Vh, ST_C128, Rh, T, (int64_t)nb * 2, n3, A2.invmu, 1.0, 0, Wp, ST_C128, st);
+    if (rc) return rc;
+  }
+  // Outer step 3: corrected periodic solve, stored, then inverse transforms.
+  {
+    InnerIO io;
+    io.sO = A1.sigB;
+    io.seedB = p->seed[0];
+    io.seedA = p->seed[1];
+    io.sigTB = p->sig[0];
+    io.sigTA = p->sig[1];
+    io.in = W0;
+    io.in_kind = T;
+    io.PO = Rh;
+    io.PO_kind = T;
+    io.alpha0 = A1.genB0;
+    io.alpha1 = A1.genB1;
+    io.out = W0;
+    io.out_kind = T;
+    rc = inner_solve(p, lv, io, st);
+    if (rc) return rc;
+  }
+  return HELM_OK;
+}
+
 // Full solve of one precision pass: u (+)= A^{-1} x.
 int solve_once(helm_plan* p, const void* x, int x_kind, double2* u, int accumulate, int nb, bool fp32,
                hipStream_t st) {
@@ -1151,118 +1403,9 @@ int solve_once(helm_plan* p, const void* x, int x_kind, double2* u, int accumula
   if (rc) return rc;
   rc = run_fft(p, A2, -1, fp32, W1, T, W0, T, (int64_t)nb * n1, n3, A2.invmu, 1.0, 0, W2 == W1 ? W0 : W2, T, st);
   if (rc) return rc;
-  Level lv{nb, n1, n2, n3, &A2, w2};
-  double2* Vh = p->P0.as<double2>();  // [nb][2][n2][n3] scratch planes
-  double2* Vp = p->P1.as<double2>();
-  double2* Wp = p->P2.as<double2>();
-  double2* Rh = p->P3.as<double2>();
-  const double2* d_null = nullptr;
-  (void)d_null;
-  // Boundary steps from the plan's tables for this many right-hand sides?
-  const bool cap = p->cap_min_nb > 0 && nb >= p->cap_min_nb;
-  // Outer step 1: v_b.
-  {
-    InnerIO io;
-    io.capS2 = cap;
-    io.sO = A1.sigB;
-    io.seedB = p->seed[0];
-    io.seedA = p->seed[1];
-    io.sigTB = p->sig[0];
-    io.sigTA = p->sig[1];
-    io.in = W0;
-    io.in_kind = T;
-    io.rhoL0 = A1.redB0;
-    io.rhoL1 = A1.redB1;
-    rc = inner_solve(p, lv, io, st);
-    if (rc) return rc;
-    rc = sum_to_planes(p, lv, Vh, st);
-    if (rc) return rc;
-    rc = run_fft(p, A2, +1, false, Vh, ST_C128, Vp, ST_C128, (int64_t)nb * 2, n3, nullptr, 1.0 / n2, 0,
-                 Wp, ST_C128, st);
-    if (rc) return rc;
-  }
-  // Outer step 2: r = C_1 v_b, w_b.
-  {
-    OuterMidArgs om;
-    om.skip = p->skip_cur;
-    om.nb = nb;
-    om.n2 = n2;
-    om.n3 = n3;
-    om.a = Vp;
-    om.c = nullptr;
-    om.r = Wp;
-    om.d1 = A1.bd;
-    om.w2 = w2;
-    om.h2 = A2.h;
-    om.h3 = p->hL;
-    om.k2Lo = corner_h(A2.glo, A2.h);
-    om.k2Hi = corner_h(A2.ghi, A2.h);
-    om.k3Lo = p->kLo;
-    om.k3Hi = p->kHi;
-    HCHK(timed(p, K_OUTER_MID, (double)nb * 2 * plane * sizeof(double2) * 3, st, [&] { return launch_outer_mid(om, st); }));
-    if (cap) {
-      // w_b = sum_l V1b[:, l] A_l^{-1} g_l with the inner absorbing
-      // eigenvectors: A_l^{-1} = (V2 (x) I) blockdiag_m T_lm^{-1} (V2^T (x) I),
-      // so w_b = (V2 (x) I) H_m (V2^T (x) I) r with the table H of
-      // sum_l V1b[k, l] V1b[k', l] T_lm^{-1} per inner mode m
-      rc = dense_pass(p, n2, n3, (int64_t)nb * 2, A2.Vd, Wp, ST_C128, Rh, ST_C128, 0, false, st);
-      if (rc) return rc;
-      rc = cap_apply(p, p->capH0, p->capH1, nb, n2, Rh, 2 * plane, n3, plane, Vh, 2 * plane, n3, plane, st);
-      if (rc) return rc;
-      rc = dense_pass(p, n2, n3, (int64_t)nb * 2, A2.VTd, Vh, ST_C128, Wp, ST_C128, 0, false, st);
-      if (rc) return rc;
-    } else {
-      rc = run_fft(p, A2, -1, false, Wp, ST_C128, Rh, ST_C128, (int64_t)nb * 2, n3, A2.invmu, 1.0, 0, Vh,
-                   ST_C128, st);
-      if (rc) return rc;
-      InnerIO io;
-      io.sO = A1.sigA;
-      io.seedB = p->seed[2];
-      io.seedA = p->seed[3];
-      io.sigTB = p->sig[2];
-      io.sigTA = p->sig[3];
-      io.PO = Rh;
-      io.alpha0 = A1.va0d;
-      io.alpha1 = A1.va1d;
-      io.rhoL0 = A1.va0d;
-      io.rhoL1 = A1.va1d;
-      rc = inner_solve(p, lv, io, st);
-      if (rc) return rc;
-      rc = sum_to_planes(p, lv, Vh, st);
-      if (rc) return rc;
-      rc = run_fft(p, A2, +1, false, Vh, ST_C128, Wp, ST_C128, (int64_t)nb * 2, n3, nullptr, 1.0 / n2, 0,
-                   Rh, ST_C128, st);
-      if (rc) return rc;
-    }
-    // q = C_1 (v_b + w_b), transformed along x_2 and scaled by 1/mu_2; stored
-    // in the lines' storage type, as the rank-2 rows of the Step-3 lines
-    om.a = Vp;
-    om.c = Wp;
-    om.r = Vh;
-    HCHK(timed(p, K_OUTER_MID, (double)nb * 2 * plane * sizeof(double2) * 3, st, [&] { return launch_outer_mid(om, st); }));
-    rc = run_fft(p, A2, -1, false, Vh, ST_C128, Rh, T, (int64_t)nb * 2, n3, A2.invmu, 1.0, 0, Wp, ST_C128, st);
-    if (rc) return rc;
-  }
-  // Outer step 3: corrected periodic solve, stored, then inverse transforms.
-  {
-    InnerIO io;
-    io.capS2 = cap;
-    io.sO = A1.sigB;
-    io.seedB = p->seed[0];
-    io.seedA = p->seed[1];
-    io.sigTB = p->sig[0];
-    io.sigTA = p->sig[1];
-    io.in = W0;
-    io.in_kind = T;
-    io.PO = Rh;
-    io.PO_kind = T;
-    io.alpha0 = A1.genB0;
-    io.alpha1 = A1.genB1;
-    io.out = W0;
-    io.out_kind = T;
-    rc = inner_solve(p, lv, io, st);
-    if (rc) return rc;
-  }
+  const Level lv{nb, n1, n2, n3, &A2, w2};
+  rc = boundary_modal(p, nb) ? solve_modal(p, lv, T, st) : solve_lines(p, lv, T, st);
+  if (rc) return rc;
   rc = run_fft(p, A2, +1, fp32, W0, T, W1, T, (int64_t)nb * n1, n3, nullptr, 1.0 / n2, 0, W2 == W1 ? W0 : W2,
                T, st);
   if (rc) return rc;
@@ -1588,8 +1731,7 @@ int capture_solve(helm_plan* p, const double2* F, double2* U, int nb, hipStream_
 
 // How the boundary steps of a solve of nrhs right-hand sides run.
 int boundary_used(const helm_plan* p, int nrhs) {
-  return (p->dim == 3 && !p->dense && p->cap_min_nb > 0 && nrhs >= p->cap_min_nb) ? HELM_BOUNDARY_TABLES
-                                                                                   : HELM_BOUNDARY_LINES;
+  return (p->dim == 3 && !p->dense && boundary_modal(p, nrhs)) ? HELM_BOUNDARY_TABLES : HELM_BOUNDARY_LINES;
 }
 
 // Refinement on the host: while the residual exceeds tol, solve for the
@@ -1857,101 +1999,115 @@ bool tune_lookup(const std::string& path, const std::string& key, int* choice) {
 }
 
 // ---------------------------------------------------------------------------
-// Boundary operator tables (3D).  W_l^{kk'} = sum_m V2b[k,m] V2b[k',m]
-// (T^{BA}_lm)^{-1} maps the inner boundary vectors to the inner Step-2
-// result of outer mode l; H_m^{kk'} = sum_l V1b[k,l] V1b[k',l] (T^{AA}_lm)^{-1}
-// maps the inner absorbing mode m of the outer boundary planes to that of the
-// outer Step-2 result.  Column x' of each is the reduction of the line
-// solutions with the unit right-hand side e_{x'}: one line launch per k'
-// with nL "right-hand sides".
+// Tables of the boundary steps in the eigenbasis of the last axis (3D)
 // ---------------------------------------------------------------------------
-int build_boundary_tables(helm_plan* p) {
+// Largest h sum_i |v_i|^2 of the last axis's eigenvectors (v^T M v = 1) that the
+// eigenbasis is used for.  It is the factor by which the transforms to and from
+// the basis can amplify rounding errors, 1 for a real pencil, 3 to 6 for
+// absorbing faces at 8 or more points per wavelength; it grows without bound
+// towards a defective pencil, where line sweeps lose nothing.
+constexpr double kModalCond = 64.0;
+
+size_t modal_bytes(const helm_plan* p) {
+  const size_t n1 = p->ax[0].n, n2 = p->ax[1].n, nL = p->nL;
+  return sizeof(double2) * (2 * nL + 2 * nL * nL + 3 * (n1 + n2) * nL + 2 * n2 * n2);
+}
+
+// Builds the tables; HELM_ENOCONV when the last axis has no usable eigenbasis.
+int build_modal(helm_plan* p) {
   const PAxis& A1 = p->ax[0];
   const PAxis& A2 = p->ax[1];
   const int n1 = A1.n, n2 = A2.n, nL = p->nL;
-  std::vector<double2> w((size_t)3 * (n1 + n2));
-  for (int m = 0; m < n2; ++m) {
-    w[m] = hd2(A2.va0[m] * A2.va0[m]);
-    w[n2 + m] = hd2(A2.va0[m] * A2.va1[m]);
-    w[2 * n2 + m] = hd2(A2.va1[m] * A2.va1[m]);
+  const size_t nn = (size_t)nL * nL, mm = (size_t)n2 * n2;
+  const double2 glo = p->glo[2], ghi = p->ghi[2];
+  std::vector<cd> lam, v0, v1, lamlo, vfull;
+  DevMem V, t1, t2, nrm;
+  HCHK(V.ensure(nn * sizeof(double2)));
+  int rc;
+  if (p->opt.eigen == HELM_EIGEN_HOST) {
+    rc = eig1d(nL, p->hL, cd(glo.x, glo.y), cd(ghi.x, ghi.y), lam, v0, v1, &vfull, &lamlo);
+    if (rc) return rc;
+    std::vector<double2> hv(nn);
+    for (size_t i = 0; i < nn; ++i) hv[i] = hd2(vfull[i]);
+    HCHK(upload(V.p, hv.data(), nn * sizeof(double2)));
+  } else {
+    EigVecOut vo{};
+    vo.Vd = V.as<double2>();
+    rc = eig1d_device(nL, p->hL, cd(glo.x, glo.y), cd(ghi.x, ghi.y), lam, v0, v1, lamlo, &vo, nullptr);
+    if (rc) return rc;
   }
-  double2* d1 = w.data() + 3 * n2;
-  for (int l = 0; l < n1; ++l) {
-    d1[l] = hd2(A1.va0[l] * A1.va0[l]);
-    d1[n1 + l] = hd2(A1.va0[l] * A1.va1[l]);
-    d1[2 * n1 + l] = hd2(A1.va1[l] * A1.va1[l]);
+  HCHK(nrm.ensure(nL * sizeof(double)));
+  HCHK(launch_col_norms(V.as<double2>(), nL, p->hL, nrm.as<double>(), nullptr));
+  std::vector<double> hn(nL);
+  HCHK(hipMemcpy(hn.data(), nrm.p, nL * sizeof(double), hipMemcpyDeviceToHost));
+  for (double x : hn)
+    if (!(x <= kModalCond)) return HELM_ENOCONV;
+  HCHK(p->modal.ensure(modal_bytes(p)));
+  double2* d = p->modal.as<double2>();
+  std::vector<double2> hl(2 * (size_t)nL);
+  for (int i = 0; i < nL; ++i) {
+    hl[i] = hd2(lam[i]);
+    hl[nL + i] = hd2(lamlo[i]);
   }
-  DevMem wt;
-  HCHK(wt.ensure(w.size() * sizeof(double2)));
-  HCHK(upload(wt.p, w.data(), w.size() * sizeof(double2)));
-  const double2* c = wt.as<double2>();        // c00, c01, c11 over m
-  const double2* dd = c + 3 * (size_t)n2;     // d00, d01, d11 over l
-  const size_t blkW = (size_t)nL * n1 * 2 * nL, blkH = (size_t)nL * n2 * 2 * nL;
-  const size_t esz = p->cap_fp32 ? sizeof(float2) : sizeof(double2);
-  HCHK(p->capW.ensure(2 * blkW * esz));
-  HCHK(p->capH.ensure(2 * blkH * esz));
-  p->capW0 = p->capW.p;
-  p->capW1 = static_cast<char*>(p->capW.p) + blkW * esz;
-  p->capH0 = p->capH.p;
-  p->capH1 = static_cast<char*>(p->capH.p) + blkH * esz;
-  DevMem part, stage;  // line partials; one table block in the reductions' layout
-  HCHK(part.ensure(std::max(part_elems(1, nL, n1, n2, nL), part_elems(2, nL, n1, n2, nL)) * sizeof(double2)));
-  HCHK(stage.ensure(std::max(blkW, blkH) * sizeof(double2)));
-  LineArgs base;
-  base.nb = nL;
-  base.nO = n1;
-  base.nI = n2;
-  base.nL = nL;
-  base.hL = p->hL;
-  base.kLo = p->kLo;
-  base.kHi = p->kHi;
-  base.unit_rhs = 1;
-  base.part = part.as<double2>();
-  for (int kp = 0; kp < 2; ++kp) {
-    LineArgs la = base;  // W: lines of the (B, A) family, reduced over m
-    la.sTab = p->sig[1];
-    la.piv = p->seed[1];
-    la.red = 1;
-    la.rho0 = kp ? c + n2 : c;
-    la.rho1 = kp ? c + 2 * n2 : c + n2;
-    tiles_for(p, 1, nL, n1, n2, nL, &la.tile, &la.ntiles);
-    HCHK(launch_lines(la, nullptr));
-    HCHK(launch_sum_partials(base.part, nL * n1, la.ntiles, nL, stage.as<double2>(), nullptr, nullptr));
-    HCHK(launch_cap_reorder(stage.as<double2>(), const_cast<void*>(kp ? p->capW1 : p->capW0), n1, nL,
-                            p->cap_fp32 != 0, nullptr));
-  }
-  for (int kp = 0; kp < 2; ++kp) {
-    LineArgs la = base;  // H: lines of the (A, A) family, reduced over l
-    la.sTab = p->sig[3];
-    la.piv = p->seed[3];
-    la.red = red_l_mode(p);
-    la.rho0 = kp ? dd + n1 : dd;
-    la.rho1 = kp ? dd + 2 * n1 : dd + n1;
-    tiles_for(p, 2, nL, n1, n2, nL, &la.tile, &la.ntiles);
-    HCHK(launch_lines(la, nullptr));
-    HCHK(launch_sum_partials(base.part, nL * n2, la.ntiles, nL, stage.as<double2>(), nullptr, nullptr));
-    HCHK(launch_cap_reorder(stage.as<double2>(), const_cast<void*>(kp ? p->capH1 : p->capH0), n2, nL,
-                            p->cap_fp32 != 0, nullptr));
-  }
+  HCHK(upload(d, hl.data(), hl.size() * sizeof(double2)));
+  p->mlam = d;
+  p->mlamlo = d + nL;
+  double2* MV = d + 2 * nL;
+  double2* MVT = MV + nn;
+  double2* S = MVT + nn;
+  double2* H = S + 3 * (size_t)n1 * nL;
+  double2* G1 = H + 3 * (size_t)n2 * nL;
+  double2* G2 = G1 + mm;
+  p->mMV = MV;
+  p->mMVT = MVT;
+  p->mS = S;
+  p->mH = H;
+  p->mG1 = G1;
+  p->mG2 = G2;
+  HCHK(launch_mass_vec(V.as<double2>(), nL, p->hL, MV, MVT, nullptr));
+  HCHK(launch_modal_table(p->sig[1], 1, n2, n2, n1, nL, p->mlam, p->mlamlo, A2.va0d, A2.va1d, S, nullptr));
+  HCHK(launch_modal_table(p->sig[3], n2, 1, n1, n2, nL, p->mlam, p->mlamlo, A1.va0d, A1.va1d, H, nullptr));
+  // a = V_2^T M_2 F^{-1} v^: the inverse DFT of the columns of M_2 V_2; back,
+  // F M_2 V_2 / mu: their DFT, transposed for the product
+  HCHK(t1.ensure(mm * sizeof(double2)));
+  HCHK(t2.ensure(mm * sizeof(double2)));
+  HCHK(launch_mass_vec(static_cast<const double2*>(A2.Vd), n2, A2.h, t1.as<double2>(), nullptr, nullptr));
+  DevMem bt;  // the chirp-z buffer of these transforms
+  if (A2.blue) HCHK(bt.ensure((size_t)A2.M * n2 * sizeof(double2)));
+  std::swap(p->BT1.p, bt.p);
+  std::swap(p->BT1.bytes, bt.bytes);
+  rc = run_fft(p, A2, +1, false, t1.p, ST_C128, G1, ST_C128, 1, n2, nullptr, 1.0 / n2, 0, G2, ST_C128, nullptr);
+  if (!rc) rc = run_fft(p, A2, -1, false, t1.p, ST_C128, t2.p, ST_C128, 1, n2, A2.invmu, 1.0, 0, G2, ST_C128, nullptr);
+  std::swap(p->BT1.p, bt.p);
+  std::swap(p->BT1.bytes, bt.bytes);
+  if (rc) return rc;
+  HCHK(launch_transpose(t2.as<double2>(), n2, G2, nullptr));
   HCHK(hipDeviceSynchronize());
   return HELM_OK;
 }
 
 // Times (ms, best of 3 after a warm-up) of the boundary work of one 3D solve
-// of nb right-hand sides that the tables replace: 5 Step-2-like line sweeps
-// (measured as one sweep times 5) against two capW products, one capH
-// product and the two inner eigenvector transforms of the boundary planes.
-int measure_boundary(helm_plan* p, int nb, double* t_lines, double* t_tab) {
+// of nb right-hand sides in both forms: the six line sweeps that the
+// eigenbasis saves (one measured, times 6) against its chain of products.
+int measure_boundary(helm_plan* p, int nb, double* t_lines, double* t_modal) {
   const PAxis& A2 = p->ax[1];
   const int n1 = p->ax[0].n, n2 = A2.n, nL = p->nL;
-  const int64_t per = 2 * (int64_t)nL, plane = (int64_t)n2 * nL;
-  DevMem pi, part, pa, pb;
-  HCHK(pi.ensure((size_t)nb * n1 * per * sizeof(double2)));
+  const size_t e1 = (size_t)nb * n1 * 2 * nL, e2 = (size_t)nb * n2 * 2 * nL;
+  DevMem pi, part, w;
+  HCHK(pi.ensure(e1 * sizeof(double2)));
   HCHK(part.ensure(part_elems(1, nb, n1, n2, nL) * sizeof(double2)));
-  HCHK(pa.ensure((size_t)nb * 2 * plane * sizeof(double2)));
-  HCHK(pb.ensure((size_t)nb * 2 * plane * sizeof(double2)));
+  HCHK(w.ensure((3 * e1 + 4 * e2) * sizeof(double2)));
   HCHK(hipMemset(pi.p, 0x3f, pi.bytes));  // finite values of order 1e-3
-  HCHK(hipMemset(pa.p, 0x3f, pa.bytes));
+  HCHK(hipMemset(w.p, 0x3f, w.bytes));
+  ModalBufs mb;
+  double2* wp = w.as<double2>();
+  mb.part1 = wp;
+  mb.a1 = wp + e1;
+  mb.q = mb.a1 + e1;
+  mb.part2 = mb.q + e1;
+  mb.v0 = mb.q + e1 + e2;
+  mb.v1 = mb.v0 + e2;
+  mb.v2 = mb.v1 + e2;
   LineArgs s2;
   s2.nb = nb;
   s2.nO = n1;
@@ -1975,46 +2131,32 @@ int measure_boundary(helm_plan* p, int nb, double* t_lines, double* t_tab) {
     HCHK(launch_lines(s2, nullptr));
     return HELM_OK;
   };
-  auto tab = [&]() -> int {
-    const int64_t gs = (int64_t)n1 * per;
-    for (int k = 0; k < 2; ++k) {
-      const int rc = cap_apply(p, p->capW0, p->capW1, nb, n1, pi.as<double2>(), gs, per, nL, part.as<double2>(),
-                               gs, per, nL, nullptr);
-      if (rc) return rc;
-    }
-    int rc = dense_pass(p, n2, nL, (int64_t)nb * 2, A2.Vd, pa.p, ST_C128, pb.p, ST_C128, 0, false, nullptr);
-    if (rc) return rc;
-    rc = cap_apply(p, p->capH0, p->capH1, nb, n2, pb.as<double2>(), 2 * plane, nL, plane, pa.as<double2>(),
-                   2 * plane, nL, plane, nullptr);
-    if (rc) return rc;
-    return dense_pass(p, n2, nL, (int64_t)nb * 2, A2.VTd, pa.p, ST_C128, pb.p, ST_C128, 0, false, nullptr);
-  };
-  hipEvent_t e0, e1;
-  HCHK(hipEventCreate(&e0));
-  if (hipEventCreate(&e1) != hipSuccess) {
-    (void)hipEventDestroy(e0);
+  hipEvent_t e[2];
+  HCHK(hipEventCreate(&e[0]));
+  if (hipEventCreate(&e[1]) != hipSuccess) {
+    (void)hipEventDestroy(e[0]);
     return HELM_EDEVICE;
   }
   int rc = HELM_OK;
   double best[2] = {1e30, 1e30};
   for (int which = 0; which < 2 && !rc; ++which) {
     for (int rep = 0; rep < 4 && !rc; ++rep) {
-      if (hipEventRecord(e0, nullptr) != hipSuccess) { rc = HELM_EDEVICE; break; }
-      rc = which == 0 ? lines() : tab();
+      if (hipEventRecord(e[0], nullptr) != hipSuccess) { rc = HELM_EDEVICE; break; }
+      rc = which == 0 ? lines() : modal_chain(p, mb, nb, false, nullptr);
       if (rc) break;
       float ms = 0;
-      if (hipEventRecord(e1, nullptr) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-          hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
+      if (hipEventRecord(e[1], nullptr) != hipSuccess || hipEventSynchronize(e[1]) != hipSuccess ||
+          hipEventElapsedTime(&ms, e[0], e[1]) != hipSuccess) {
         rc = HELM_EDEVICE;
         break;
       }
       if (rep > 0) best[which] = std::min(best[which], (double)ms);
     }
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  *t_lines = 5.0 * best[0];
-  *t_tab = best[1];
+  (void)hipEventDestroy(e[0]);
+  (void)hipEventDestroy(e[1]);
+  *t_lines = 6.0 * best[0];
+  *t_modal = best[1];
   return rc;
 }
 
@@ -2266,53 +2408,52 @@ int setup_boundary_tables(helm_plan* p) {
   const bool forced = p->opt.boundary == HELM_BOUNDARY_TABLES;
   const int n1 = p->ax[0].n, n2 = p->ax[1].n, nL = p->nL;
   if ((int64_t)nL * n1 * n2 >= 0x7fffffffLL) return forced ? HELM_EUNSUPPORTED : HELM_OK;
-  const double bytes = (p->opt.precision == HELM_PREC_MIXED ? 32.0 : 64.0) * nL * nL * (double)(n1 + n2);
   size_t fr = 0, tot = 0;
   if (hipMemGetInfo(&fr, &tot) != hipSuccess) return HELM_EDEVICE;
   const double budget = std::min(32.0 * (double)(1ull << 30), 0.25 * (double)fr);
-  if (!forced && bytes > budget) return HELM_OK;
+  if (!forced && (double)modal_bytes(p) > budget) return HELM_OK;
   const std::string key = tune_key(p);
   int cached = -1;
   if (!forced && !p->tune_path.empty() && tune_lookup(p->tune_path, key, "boundary cap_min_nb=", &cached) &&
       cached == 0)
     return HELM_OK;  // measured before: the tables never pay for this shape
-  // the mixed-precision path keeps its tables in complex64, like its other
-  // bulk data (they are applied to FP64 boundary vectors with FP64 sums)
-  p->cap_fp32 = p->opt.precision == HELM_PREC_MIXED;
-  int rc = build_boundary_tables(p);
+  int rc = build_modal(p);
+  // no usable eigenbasis (or, unless asked for, no memory for it): line sweeps
+  if (rc == HELM_ENOCONV || (rc == HELM_ENOMEM && !forced)) {
+    (void)hipGetLastError();
+    p->modal.release();
+    return HELM_OK;
+  }
   if (rc) return rc;
   if (forced) {
-    p->cap_min_nb = 1;
+    p->modal_min_nb = 1;
     return HELM_OK;
   }
   if (cached > 0) {
-    p->cap_min_nb = cached;
+    p->modal_min_nb = cached;
     return HELM_OK;
   }
   // time both forms at 1 and 16 right-hand sides; both grow linearly with nb
-  rc = measure_boundary(p, 1, &p->cap_ms[0], &p->cap_ms[2]);
-  if (!rc) rc = measure_boundary(p, 16, &p->cap_ms[1], &p->cap_ms[3]);
+  double* ms = p->modal_ms;
+  rc = measure_boundary(p, 1, &ms[0], &ms[2]);
+  if (!rc) rc = measure_boundary(p, 16, &ms[1], &ms[3]);
   if (rc) return rc;
-  const double bl = (p->cap_ms[1] - p->cap_ms[0]) / 15.0, al = p->cap_ms[0] - bl;
-  const double bt = (p->cap_ms[3] - p->cap_ms[2]) / 15.0, at = p->cap_ms[2] - bt;
+  const double bl = (ms[1] - ms[0]) / 15.0, al = ms[0] - bl;
+  const double bt = (ms[3] - ms[2]) / 15.0, at = ms[2] - bt;
   int nmin = 0;
-  if (p->cap_ms[2] < p->cap_ms[0]) {
+  if (ms[2] < ms[0]) {
     nmin = 1;
   } else if (bl > bt) {
     const double x = (at - al) / (bl - bt);  // tables win above x right-hand sides
     nmin = x < 1e6 ? (int)std::floor(x) + 1 : 0;
   }
-  p->cap_min_nb = nmin;
-  if (nmin == 0) {  // never pays: give the memory back
-    p->capW.release();
-    p->capH.release();
-    p->capW0 = p->capW1 = p->capH0 = p->capH1 = nullptr;
-  }
+  p->modal_min_nb = nmin;
+  if (nmin == 0) p->modal.release();  // never pays: give the memory back
   if (!p->tune_path.empty()) {
     FILE* f = std::fopen(p->tune_path.c_str(), "a");
     if (f) {
       std::fprintf(f, "helm-tune %s boundary cap_min_nb=%d lines_ms_1=%.6g lines_ms_16=%.6g tables_ms_1=%.6g "
-                   "tables_ms_16=%.6g\n", key.c_str(), nmin, p->cap_ms[0], p->cap_ms[1], p->cap_ms[2], p->cap_ms[3]);
+                   "tables_ms_16=%.6g\n", key.c_str(), nmin, ms[0], ms[1], ms[2], ms[3]);
       std::fclose(f);
     }
   }
@@ -2716,6 +2857,11 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
   if (want_tab) {
     const int brc = setup_boundary_tables(p.get());
     if (brc != HELM_OK) return brc;
+    if (!dense_ok) {  // the inner eigenvectors served the tables only
+      PAxis& a2 = p->ax[1];
+      a2.vmat.release();
+      a2.Vd = a2.VTd = a2.Vf = a2.VTf = nullptr;
+    }
   }
   if (tf != HELM_TRANSFORM_DENSE) {
     const int frc = tune_fft_tile(p.get());
@@ -2807,7 +2953,7 @@ const char* helm_kernel_name(int k) {
   static const char* names[HELM_NKERNELS] = {
       "fft_pass_kernel<double2>", "fft_pass_kernel<float2>", "lines_kernel",    "inner_mid_kernel",
       "sum_to_planes_kernel",     "outer_mid_kernel",        "residual_kernel", "dense_kernel",
-      "cap_apply_kernel"};
+      "modal_sum_kernel"};
   return (k >= 0 && k < HELM_NKERNELS) ? names[k] : nullptr;
 }
 
