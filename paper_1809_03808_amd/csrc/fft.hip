@@ -212,11 +212,39 @@ constexpr int narrow_threads(int L) { return L >= 512 ? 256 : (L >= 256 ? 128 : 
 template <typename C> constexpr int narrow_w(int L) {
   return pow2_floor(std::max(narrow_threads(L) * 8 / L, 16 / (int)sizeof(C)));
 }
+//
+// Single passes over 1024 to 4096 points: the 128 KB tile holds 2 to 8
+// complex128 columns, a 64 KB tile (WO = -2, 512 threads, two blocks per compute
+// unit) half of them; the plan's tuner times both against two passes.
+constexpr int kHalf = -2;
 template <int L, typename C, int WO> constexpr int tile_w_of() {
-  return WO < 0 ? narrow_w<C>(L) : (WO ? WO : tile_w<C>(L));
+  return WO == kHalf ? tile_w<C>(L) / 2 : (WO < 0 ? narrow_w<C>(L) : (WO ? WO : tile_w<C>(L)));
 }
-template <int L, int WO> constexpr int threads_for() { return WO < 0 ? narrow_threads(L) : threads_of(L); }
-template <int L, typename C, int WO> constexpr int min_waves_of() { return WO > 0 ? 8 : 1; }
+template <int L, int WO> constexpr int threads_for() {
+  return WO == kHalf ? 512 : (WO < 0 ? narrow_threads(L) : threads_of(L));
+}
+template <int L, typename C, int WO> constexpr int min_waves_of() { return WO > 0 ? 8 : (WO == kHalf ? 4 : 1); }
+
+// LDS position of element (row, w) of a tile.  Rows of less than 128 bytes
+// (half the bank cycle) get one pad element per 8: the first stage writes every
+// eighth row, which would otherwise meet in the same banks (8 W elements apart;
+// padded 9 W).
+template <int W, typename C> constexpr bool padded() { return W * (int)sizeof(C) < 128; }
+template <int W, typename C> __device__ inline int lpos(int row, int w) {
+  const int e = row * W + w;
+  return padded<W, C>() ? e + (e >> 3) : e;
+}
+template <int L, int W, typename C> constexpr int lds_elems() { return padded<W, C>() ? L * W + (L * W >> 3) : L * W; }
+
+// Blocks are dealt to the 8 XCDs in turn, each with its own L2.  Tiles of row
+// segments shorter than a cache line are renumbered so that an XCD takes a
+// contiguous range of them: neighbours then find the rest of their lines in
+// its L2.  A bijection on [0, n) for any n.
+template <int W, typename C> __device__ inline int64_t tile_of_block(int64_t b, int64_t n) {
+  if constexpr (W * (int)sizeof(C) >= 128) return b;
+  const int64_t q = n / 8, r = n % 8, x = b % 8, k = b / 8;
+  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
+}
 
 // One Stockham stage of radix R with Ns points already combined.  Thread
 // tid of NT owns butterflies t = tid + q*NT, t -> (j = t / W,
@@ -233,7 +261,7 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
   constexpr bool STOREG = LAST && GOUT;   // this stage writes global memory
   constexpr int LR = L / R;
   constexpr int NBF = LR * W;
-  static_assert(NT % W == 0 && L * W * (int)sizeof(C) <= 160 * 1024, "tile does not fit the thread block or LDS");
+  static_assert(NT % W == 0 && lds_elems<L, W, C>() * (int)sizeof(C) <= 160 * 1024, "tile does not fit the thread block or LDS");
   constexpr int NB = (NBF + NT - 1) / NT;
   const int w = tid % W;
   const int64_t col = i0 + w;
@@ -264,7 +292,7 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
           }
           v[q][r] = x;
         } else {
-          v[q][r] = sm[row * W + w];
+          v[q][r] = sm[lpos<W, C>(row, w)];
         }
       }
     }
@@ -285,9 +313,28 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
       const int base = (j / Ns) * Ns * R + k;
       if constexpr (!STOREG) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) sm[(base + r * Ns) * W + w] = v[q][r];
+        for (int r = 0; r < R; ++r) sm[lpos<W, C>(base + r * Ns, w)] = v[q][r];
       } else {
         if (colok) {
+          // Accumulating over 1024 and more points, one block of 1024 threads
+          // per compute unit: all old values are loaded before the first
+          // store (a store may alias the next load, so loads between the
+          // stores are waited for one by one; 2048^2 mixed: 470 -> 458 us a
+          // solve).  Smaller tiles have other blocks to hide those waits, and
+          // the registers would cost occupancy; in the streaming pass these
+          // loads would wait for the prefetch (512^3 x 4: 4.5 -> 5.3 ms).
+          constexpr bool EARLY = L > 512 && !REG;
+          const bool early = EARLY && p.acc && p.out_kind == ST_C128;
+          double2 old[EARLY ? R : 1];
+          if (EARLY && early) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              const int kk = base + r * Ns;
+              const bool ok = !p.cout || col / p.chirp_S + p.chirp_na * kk < p.chirp_n;
+              const int64_t oi = oq * p.out_so1 + orr * p.out_so2 + kk * p.out_sk + col;
+              old[EARLY ? r : 0] = ok ? reinterpret_cast<const double2*>(out)[oi] : make_double2(0, 0);
+            }
+          }
 #pragma unroll
           for (int r = 0; r < R; ++r) {
             const int kk = base + r * Ns;  // output frequency of this pass
@@ -311,7 +358,11 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
             if (p.scale) s *= p.scale[mi];
             y.x = (typename RealOf<C>::T)(y.x * s);
             y.y = (typename RealOf<C>::T)(y.y * s);
-            store_as<C>(out, oq * p.out_so1 + orr * p.out_so2 + kk * p.out_sk + col, p.out_kind, y, p.acc);
+            const int64_t oi = oq * p.out_so1 + orr * p.out_so2 + kk * p.out_sk + col;
+            if (EARLY && early)
+              reinterpret_cast<double2*>(out)[oi] = make_double2((double)y.x + old[EARLY ? r : 0].x, (double)y.y + old[EARLY ? r : 0].y);
+            else
+              store_as<C>(out, oi, p.out_kind, y, p.acc);
           }
         }
       }
@@ -337,9 +388,9 @@ __global__ __launch_bounds__((threads_for<L, WO>()), (min_waves_of<L, C, WO>()))
                                                                                                      const void* in,
                                                                                                      void* out) {
   constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
-  __shared__ C sm[nstages(L) > 1 ? L * W : 1];
+  __shared__ C sm[nstages(L) > 1 ? lds_elems<L, W, C>() : 1];
   if (p.skip && *p.skip) return;
-  const int64_t blk = blockIdx.x;
+  const int64_t blk = tile_of_block<W, C>(blockIdx.x, gridDim.x);
   const int64_t o = blk / p.ntile;
   const int64_t i0 = (blk - o * p.ntile) * W;
   const int64_t oq = o / p.od, orr = o - oq * p.od;
@@ -377,8 +428,8 @@ __global__ __launch_bounds__(threads_of(L), 1) void fft_stream_kernel(PassDev p0
   constexpr int LR = L / R0;
   constexpr int NB = LR * W / NT;
   static_assert(NB * NT == LR * W, "the first stage's butterflies fill the block");
-  static_assert((L * W + L) * sizeof(C) + L * sizeof(double) <= 160 * 1024, "LDS");
-  __shared__ C sm[L * W];
+  static_assert((lds_elems<L, W, C>() + L) * sizeof(C) + L * sizeof(double) <= 160 * 1024, "LDS");
+  __shared__ C sm[lds_elems<L, W, C>()];
   __shared__ C twl[L];
   __shared__ double scl[L];
   if (p0.skip && *p0.skip) return;
@@ -456,9 +507,9 @@ __global__ __launch_bounds__(threads_of(L), 1) void fft_stream_kernel(PassDev p0
 template <int L, typename C, int WO = 0>
 __global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassDev p, const void* in, void* out) {
   constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
-  __shared__ C sm[L * W];
+  __shared__ C sm[lds_elems<L, W, C>()];
   if (p.skip && *p.skip) return;
-  const int64_t blk = blockIdx.x;
+  const int64_t blk = tile_of_block<W, C>(blockIdx.x, gridDim.x);
   const int64_t o = blk / p.ntile;
   const int64_t i0 = (blk - o * p.ntile) * W;
   const int64_t oq = o / p.od, orr = o - oq * p.od;
@@ -466,9 +517,10 @@ __global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassD
   const C* hk = reinterpret_cast<const C*>(p.cmode);
   for (int e = threadIdx.x; e < L * W; e += NT) {
     const int d = e / W;
-    C y = cmul(sm[e], hk[orr + p.od * d]);
+    C& z = sm[lpos<W, C>(d, e % W)];
+    C y = cmul(z, hk[orr + p.od * d]);
     y.y = -y.y;
-    sm[e] = y;
+    z = y;
   }
   __syncthreads();
   PassDev q = p;
@@ -582,9 +634,9 @@ hipError_t launch_stream_L(const PassDev& p, int64_t O, const void* in, void* ou
   return hipGetLastError();
 }
 
-// small_tile: 0 the default tile, 1 the 64 KB complex64 tile, 2 the
-// streaming pass (512 points; other passes and inputs that it does not
-// take fall back to the default).
+// small_tile: 0 the default tile, 1 the 64 KB tile (complex64 at 512 points;
+// 1024 to 4096 points), 2 the streaming pass (512 points; other passes and
+// inputs that it does not take fall back to the default).
 template <typename C>
 hipError_t launch_typed(int L, const PassDev& p, int64_t O, const void* in, void* out, hipStream_t s,
                         int small_tile) {
@@ -601,7 +653,15 @@ hipError_t launch_typed(int L, const PassDev& p, int64_t O, const void* in, void
   if constexpr (sizeof(C) == sizeof(float2)) {
     if (L == 512 && small_tile == 1) return launch_L<512, C, 16>(p, O, in, out, s);
   }
+  if (small_tile == 1) {
+    if (L == 1024) return launch_L<1024, C, kHalf>(p, O, in, out, s);
+    if (L == 2048) return launch_L<2048, C, kHalf>(p, O, in, out, s);
+    if (L == 4096) return launch_L<4096, C, kHalf>(p, O, in, out, s);
+  }
   switch (L) {
+    case 1024: return launch_L<1024, C>(p, O, in, out, s);
+    case 2048: return launch_L<2048, C>(p, O, in, out, s);
+    case 4096: return launch_L<4096, C>(p, O, in, out, s);
     case 2: return launch_L<2, C>(p, O, in, out, s);
     case 4: return launch_L<4, C>(p, O, in, out, s);
     case 8: return launch_L<8, C>(p, O, in, out, s);

@@ -87,6 +87,7 @@ struct PAxis {
   double* invmu = nullptr;
   BDiff bd;
   int na = 0, nbp = 0;  // FFT split n = na * nbp (nbp = first pass length); na = 1 -> one pass
+  int half_tile = 0;    // one pass of 1024 to 4096 points: the 64 KB tile (tuned)
   // Bluestein (chirp-z) transform for lengths that are not powers of two:
   // convolution length M >= 2n - 2 (a power of two, or 9 * 2^j) split as
   // Mna * Mnbp (setup_bluestein).
@@ -484,7 +485,7 @@ FftPass with_tile(const helm_plan* p, FftPass f) {
 // (pass 1 writes `tmp`).  Per-mode complex multiplier `cmode`, real `scale`.
 int run_pow2(helm_plan* p, int L, int na, int nb, int sign, bool fp32, const void* in, int in_kind, void* out,
              int out_kind, int64_t O, int64_t S, const double* scale, double scale_c, const void* cmode,
-             int accumulate, void* tmp, int tmp_kind, const int* skip, hipStream_t st) {
+             int accumulate, void* tmp, int tmp_kind, const int* skip, hipStream_t st, int half_tile) {
   if (na <= 1) {
     Roots* r = get_roots(p, L, sign);
     if (!r) return HELM_ENOMEM;
@@ -509,8 +510,9 @@ int run_pow2(helm_plan* p, int L, int na, int nb, int sign, bool fp32, const voi
     f.cmode = cmode;
     f.skip = skip ? skip : p->skip_cur;
     f.tw = fp32 ? r->f.p : r->d.p;
+    f.small_tile = L > 512 ? half_tile : p->fft_small;
     const double by = (double)O * L * S * (esz_of(in_kind) + esz_of(out_kind));
-    HCHK(timed(p, fp32 ? K_FFT32 : K_FFT64, by, st, [&] { return launch_fft_pass(with_tile(p, f), fp32, in, out, st); }));
+    HCHK(timed(p, fp32 ? K_FFT32 : K_FFT64, by, st, [&] { return launch_fft_pass(f, fp32, in, out, st); }));
     return HELM_OK;
   }
   // four-step: L = na * nb, x = a + na b, k = c + nb d
@@ -580,7 +582,7 @@ int run_fft(helm_plan* p, const PAxis& a, int sign, bool fp32, const void* in, i
             void* tmp, int tmp_kind, hipStream_t st, const int* skip = nullptr) {
   if (!a.blue)
     return run_pow2(p, a.n, a.na, a.nbp, sign, fp32, in, in_kind, out, out_kind, O, S, scale, scale_c,
-                    nullptr, accumulate, tmp, tmp_kind, skip, st);
+                    nullptr, accumulate, tmp, tmp_kind, skip, st, a.half_tile);
   (void)tmp;
   (void)tmp_kind;
   const int si = sign < 0 ? 0 : 1;
@@ -2324,6 +2326,83 @@ int tune_fft_tile(helm_plan* p) {
   return HELM_OK;
 }
 
+// Power-of-two axes of 1024 to 4096 points: two passes of row segments of up to
+// 512 bytes, or one pass in 128 KB or 64 KB tiles, which moves the volume once
+// but in row segments of 16 to 128 bytes.  Timed per axis on a volume of the
+// plan's shape and precision; cached as "pow2<axis>=" (0 two passes, 1 and 2
+// the tiles).
+int tune_pow2(helm_plan* p) {
+  const bool fp32 = p->opt.precision == HELM_PREC_MIXED;
+  const int T = fp32 ? ST_C64 : ST_C128;
+  const size_t esz = fp32 ? sizeof(float2) : sizeof(double2);
+  const std::string key = tune_key(p);
+  int64_t N = 1;
+  for (int j = 0; j < p->dim; ++j) N *= p->grid[j];
+  for (int j = 0; j < p->nper; ++j) {
+    PAxis& A = p->ax[j];
+    if (A.blue || A.na <= 1 || A.n > 4096) continue;
+    const int na2 = A.na, nb2 = A.nbp;
+    auto choose = [&](int v) {
+      A.na = v ? 1 : na2;
+      A.nbp = v ? A.n : nb2;
+      A.half_tile = v == 2;
+    };
+    char field[16];
+    std::snprintf(field, sizeof field, "pow2%d=", j);
+    int cached = -1;
+    if (!p->tune_path.empty() && tune_lookup(p->tune_path, key, field, &cached) && cached >= 0 && cached <= 2) {
+      choose(cached);
+      continue;
+    }
+    int64_t O = 1, S = 1;
+    for (int i = 0; i < j; ++i) O *= p->grid[i];
+    for (int i = j + 1; i < p->dim; ++i) S *= p->grid[i];
+    DevMem in, out, tmp;
+    HCHK(in.ensure((size_t)N * esz));
+    HCHK(out.ensure((size_t)N * sizeof(double2)));
+    HCHK(tmp.ensure((size_t)N * esz));
+    HCHK(hipMemset(in.p, 0x3c, in.bytes));  // finite values
+    HCHK(hipMemset(out.p, 0x3c, out.bytes));
+    hipEvent_t e0, e1;
+    HCHK(hipEventCreate(&e0));
+    if (hipEventCreate(&e1) != hipSuccess) {
+      (void)hipEventDestroy(e0);
+      return HELM_EDEVICE;
+    }
+    int rc = HELM_OK;
+    double best[3] = {1e30, 1e30, 1e30};
+    for (int v = 0; v < 3 && !rc; ++v) {
+      choose(v);
+      for (int rep = 0; rep < 4 && !rc; ++rep) {
+        float ms = 0;
+        if (hipEventRecord(e0, nullptr) != hipSuccess) rc = HELM_EDEVICE;
+        // the transforms of a refinement step: storage type to storage type,
+        // and accumulating into complex128
+        if (!rc) rc = run_fft(p, A, -1, fp32, in.p, T, out.p, T, O, S, nullptr, 1.0, 0, tmp.p, T, nullptr);
+        if (!rc) rc = run_fft(p, A, +1, fp32, in.p, T, out.p, ST_C128, O, S, nullptr, 1.0, 1, tmp.p, T, nullptr);
+        if (!rc && (hipEventRecord(e1, nullptr) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                    hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+          rc = HELM_EDEVICE;
+        if (!rc && rep > 0) best[v] = std::min(best[v], (double)ms);
+      }
+    }
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    if (rc) return rc;
+    const int pick = best[1] < best[0] ? (best[2] < best[1] ? 2 : 1) : (best[2] < best[0] ? 2 : 0);
+    choose(pick);
+    if (!p->tune_path.empty()) {
+      FILE* f = std::fopen(p->tune_path.c_str(), "a");
+      if (f) {
+        std::fprintf(f, "helm-tune %s %s%d twopass_ms=%.6g tile128k_ms=%.6g tile64k_ms=%.6g\n", key.c_str(), field, pick,
+                     best[0], best[1], best[2]);
+        std::fclose(f);
+      }
+    }
+  }
+  return HELM_OK;
+}
+
 // Chirp-z transforms (axes whose length is not a power of two): the
 // convolution in two or three passes over the padded length M (row
 // segments of up to 32 columns) or in one pass with the whole M-point
@@ -2866,6 +2945,8 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
   if (tf != HELM_TRANSFORM_DENSE) {
     const int frc = tune_fft_tile(p.get());
     if (frc != HELM_OK) return frc;
+    const int prc = tune_pow2(p.get());
+    if (prc != HELM_OK) return prc;
     const int crc = tune_chirp(p.get());
     if (crc != HELM_OK) return crc;
   }
