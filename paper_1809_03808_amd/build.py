@@ -20,7 +20,8 @@ BUILD = os.path.join(ROOT, "_build")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 ARCH = os.environ.get("HELM_OFFLOAD_ARCH", "gfx950")
 
-HIP_SOURCES = ["fft.hip", "lines.hip", "boundary.hip", "stencil.hip", "dense.hip", "modal.hip", "eigdev.hip", "solver.hip"]
+HIP_SOURCES = ["fft.hip", "lines.hip", "lines_c128_reduce.hip", "lines_c128_store.hip",
+               "lines_c64_reduce.hip", "lines_c64_store.hip", "boundary.hip", "stencil.hip", "dense.hip", "modal.hip", "eigdev.hip", "solver.hip"]
 CXX_SOURCES = ["eig1d.cpp"]
 
 HIPCC_FLAGS = [

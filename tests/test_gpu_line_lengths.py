@@ -1,0 +1,50 @@
+"""Line lengths at the edges of the chunk geometry: for every lane count P the
+shortest and longest lines of each chunk length (one lane, all lanes, all but
+one lane with the long chunk), in both precisions, in 2D and in both forms and
+layouts of the 3D reductions, against banded LU."""
+
+import numpy as np
+import pytest
+
+from oracle import fem
+from paper_1809_03808_amd import helm, inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+LENGTHS = sorted({3, 4, 5, 6, 7} | {n for P in (2, 4, 8, 16, 32, 64, 128, 256)
+                                    for n in (4 * P + 1, 5 * P, 5 * P + 1, 6 * P + 2, 7 * P - 1, 7 * P + 1, 8 * P - 1)}
+                 | {2051, 2560, 3000, 3584, 4095})
+
+
+def _check(grid, prec, **kw):
+    h = (1.0 / (max(grid) - 1),) * len(grid)
+    omega = 2 * np.pi * (max(grid) - 1) / 10
+    abc = ((True, True),) * len(grid)
+    f = inputs.gaussian_batch(grid, [41, 42])
+    ref = fem.solve(grid, h, omega, abc, f.reshape(2, -1))
+    with helm.Plan(grid, h, omega, precision=prec, check=prec == helm.PREC_MIXED, **kw) as plan:
+        fd = torch.from_numpy(f).cuda()
+        ud = torch.empty_like(fd)
+        plan.solve(fd, ud)
+        u = ud.cpu().numpy().reshape(2, -1)
+    # the bars of the solver's parity tests
+    assert np.max(fem.rel_error(u, ref)) <= (1e-9 if prec == helm.PREC_FP64 else 1e-8)
+
+
+@pytest.mark.parametrize("prec", [helm.PREC_FP64, helm.PREC_MIXED])
+@pytest.mark.parametrize("n", LENGTHS)
+def test_2d_line_lengths(n, prec):
+    _check((8 if n < 700 else 4, n), prec)
+
+
+@pytest.mark.parametrize("layout", ["2", "3"])
+@pytest.mark.parametrize("boundary", [helm.BOUNDARY_LINES, helm.BOUNDARY_TABLES])
+@pytest.mark.parametrize("grid,prec", [((5, 9, 6), helm.PREC_FP64), ((9, 5, 13), helm.PREC_MIXED),
+                                       ((6, 7, 21), helm.PREC_FP64), ((10, 11, 33), helm.PREC_MIXED),
+                                       ((7, 6, 90), helm.PREC_FP64), ((9, 8, 129), helm.PREC_MIXED),
+                                       ((33, 40, 24), helm.PREC_FP64), ((4, 5, 257), helm.PREC_FP64),
+                                       ((4, 5, 450), helm.PREC_MIXED), ((3, 4, 700), helm.PREC_FP64)])
+def test_3d_line_lengths(grid, prec, boundary, layout, monkeypatch):
+    monkeypatch.setenv("HELM_RED_L_LAYOUT", layout)
+    _check(grid, prec, boundary=boundary)
