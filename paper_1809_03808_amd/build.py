@@ -21,7 +21,9 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 ARCH = os.environ.get("HELM_OFFLOAD_ARCH", "gfx950")
 
 HIP_SOURCES = ["fft.hip", "lines.hip", "lines_c128_reduce.hip", "lines_c128_store.hip",
-               "lines_c64_reduce.hip", "lines_c64_store.hip", "boundary.hip", "stencil.hip", "dense.hip", "modal.hip", "eigdev.hip", "solver.hip"]
+               "lines_c64_reduce.hip", "lines_c64_store.hip", "lines_c128_reduce_real.hip",
+               "lines_c128_store_real.hip", "lines_c64_reduce_real.hip", "lines_c64_store_real.hip",
+               "boundary.hip", "stencil.hip", "dense.hip", "modal.hip", "eigdev.hip", "solver.hip"]
 CXX_SOURCES = ["eig1d.cpp"]
 
 HIPCC_FLAGS = [

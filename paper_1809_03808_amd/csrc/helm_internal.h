@@ -171,6 +171,9 @@ struct LineArgs {
   double2* part = nullptr;
   const double2* piv = nullptr;  // [nO*nI][P] reciprocal pivot entering each lane chunk
   const double2* sTab = nullptr; // [nO*nI] sigma of every line (replaces sO + sI + sC when set)
+  // periodic branches only: every sigma is real, and the weights rho0 of a
+  // launch that reduces `in` are all equal and real
+  bool real_sigma = false;
   int tile = 0;    // lines per workgroup tile
   int ntiles = 0;  // tiles along the reduced (or flattened) index
   const int* skip = nullptr;     // device flag: the launch does nothing while *skip != 0

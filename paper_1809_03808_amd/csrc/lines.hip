@@ -5,10 +5,14 @@
 namespace helm {
 
 namespace linek {
-extern template hipError_t launch_lines_kernel<double2, true>(const LineDev&, int, int64_t, hipStream_t);
-extern template hipError_t launch_lines_kernel<double2, false>(const LineDev&, int, int64_t, hipStream_t);
-extern template hipError_t launch_lines_kernel<float2, true>(const LineDev&, int, int64_t, hipStream_t);
-extern template hipError_t launch_lines_kernel<float2, false>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<double2, true, true>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<double2, true, false>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<double2, false, true>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<double2, false, false>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<float2, true, true>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<float2, true, false>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<float2, false, true>(const LineDev&, int, int64_t, hipStream_t);
+extern template hipError_t launch_lines_kernel<float2, false, false>(const LineDev&, int, int64_t, hipStream_t);
 }  // namespace linek
 
 namespace {
@@ -165,11 +169,18 @@ hipError_t launch_lines(LineArgs a, hipStream_t s) {
   if ((a.in && a.out && a.in_kind != a.out_kind)) return hipErrorInvalidValue;
   const int kind = a.in ? a.in_kind : a.out_kind;
   if ((a.PO || a.PI) && a.r2_kind != kind) return hipErrorInvalidValue;
-  if (kind == ST_C64)
-    return d.red ? linek::launch_lines_kernel<float2, true>(d, P, blocks, s)
-                 : linek::launch_lines_kernel<float2, false>(d, P, blocks, s);
-  return d.red ? linek::launch_lines_kernel<double2, true>(d, P, blocks, s)
-               : linek::launch_lines_kernel<double2, false>(d, P, blocks, s);
+  // the SPEC kernels' conditions
+  const bool spec = a.real_sigma && (a.red ? a.in && !a.PO && !a.PI : a.PO || a.PI);
+  auto go = [&](auto t, auto sp) {
+    using T = decltype(t);
+    constexpr bool S = decltype(sp)::value;
+    return d.red ? linek::launch_lines_kernel<T, true, S>(d, P, blocks, s)
+                 : linek::launch_lines_kernel<T, false, S>(d, P, blocks, s);
+  };
+  using std::false_type;
+  using std::true_type;
+  if (kind == ST_C64) return spec ? go(float2{}, true_type{}) : go(float2{}, false_type{});
+  return spec ? go(double2{}, true_type{}) : go(double2{}, false_type{});
 }
 
 }  // namespace helm

@@ -1,9 +1,9 @@
-// Line kernels with complex64 storage: storing launches (a file per type and kind, so that
-// they compile in parallel).
+// Line kernels with complex64 storage: storing launches, the general form
+// (a file per type and kind, so that they compile in parallel).
 #include "lines_kernel.h"
 
 namespace helm {
 namespace linek {
-template hipError_t launch_lines_kernel<float2, false>(const LineDev& d, int P, int64_t blocks, hipStream_t s);
+template hipError_t launch_lines_kernel<float2, false, false>(const LineDev& d, int P, int64_t blocks, hipStream_t s);
 }  // namespace linek
 }  // namespace helm

@@ -1,0 +1,9 @@
+// Line kernels with complex64 storage: storing launches, real sigma
+// (a file per type and kind, so that they compile in parallel).
+#include "lines_kernel.h"
+
+namespace helm {
+namespace linek {
+template hipError_t launch_lines_kernel<float2, false, true>(const LineDev& d, int P, int64_t blocks, hipStream_t s);
+}  // namespace linek
+}  // namespace helm

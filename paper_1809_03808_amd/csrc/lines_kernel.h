@@ -400,8 +400,16 @@ __device__ inline int stage_pos(int e) { return e + (e >> 3); }
 // registers, so that two blocks of eight waves share a compute unit (the
 // complex64 kernel needs 131 otherwise and then spills 2; 4096^2 mixed
 // solve: line launches 0.365 -> 0.344 ms).
-template <typename T, int NT, int P, int C, bool RED, bool XR, bool BAL>
+//
+// SPEC: sigma is real (the periodic branch of every periodised axis), so the
+// off-diagonal entry and its square are (a complex product with them takes two
+// instructions instead of four), and a reducing launch has an input and no
+// rank-2 rows, and its first weight rho_0 is one real number (1/n).  These
+// are the two reductions of a 3D solve in the eigenbasis, Step 1 in 2D and the
+// storing launches of the fast method.
+template <typename T, int NT, int P, int C, bool RED, bool XR, bool BAL, bool SPEC>
 __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_kernel(LineDev a) {
+  constexpr bool RANK2 = !(RED && SPEC);
   constexpr int NW = NT / 64;
   constexpr int PW = P < 64 ? P : 64;     // lanes of one line inside a wave
   constexpr int SPW = 64 / PW;            // lines per wave
@@ -495,7 +503,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     }
     if constexpr (EARLY) {
       const uint32_t wi = (a.red == 1) ? em : el;
-      ew0 = a.rho0[wi];
+      if (!SPEC) ew0 = a.rho0[wi];
       ew1 = a.rho1[wi];
     }
     // ---- right-hand side, staged through LDS -------------------------------
@@ -505,10 +513,10 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
       const bool sv = decode_line(a, g, t, LPB, it, wslot0 + si, sb, sl, sm);
       const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
       double2 al0 = make_double2(0, 0), al1 = al0, be0 = al0, be1 = al0;
-      if (a.PO) { al0 = a.alpha0[sl]; al1 = a.alpha1[sl]; }
-      if (a.PI) { be0 = a.beta0[sm]; be1 = a.beta1[sm]; }
-      const T* po = a.PO ? reinterpret_cast<const T*>(a.PO) + (int64_t)(sb * 2) * a.nI * nL + (int64_t)sm * nL : nullptr;
-      const T* pi = a.PI ? reinterpret_cast<const T*>(a.PI) + (int64_t)((sb * a.nO + sl) * 2) * nL : nullptr;
+      if (RANK2 && a.PO) { al0 = a.alpha0[sl]; al1 = a.alpha1[sl]; }
+      if (RANK2 && a.PI) { be0 = a.beta0[sm]; be1 = a.beta1[sm]; }
+      const T* po = RANK2 && a.PO ? reinterpret_cast<const T*>(a.PO) + (int64_t)(sb * 2) * a.nI * nL + (int64_t)sm * nL : nullptr;
+      const T* pi = RANK2 && a.PI ? reinterpret_cast<const T*>(a.PI) + (int64_t)((sb * a.nO + sl) * 2) * nL : nullptr;
       // one source at a time (each lane revisits only its own staging slots),
       // so that at most NJ loads are in flight per lane
       if (a.in && PREF) {
@@ -577,7 +585,8 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
                           : RED ? (P <= 128 ? NJ : (P == 512 ? 2 : 0))
                                 : ((P >= 16 && P <= 64) ? 4 : (SEP ? 2 : 0));
       constexpr int NBAT = NB0 < NJ ? NB0 : NJ;
-      if constexpr (NBAT > 0) {
+      if constexpr (!RANK2) {
+      } else if constexpr (NBAT > 0) {
 #pragma unroll
         for (int src = 0; src < 2; ++src) {
           const T* rows = src == 0 ? po : pi;
@@ -641,8 +650,15 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     } else {
       valid = decode_line(a, g, t, LPB, it, slot, b, l, m);
     }
-    const RowCoef rc = (EARLY || EARLY_SP) ? coef_of_sigma(a, esig) : row_coef(a, l, m);
+    const double2 sig = (EARLY || EARLY_SP) ? esig : line_sigma(a, l, m);
+    RowCoef rc = coef_of_sigma(a, sig);
+    if (SPEC) rc.dint.y = 0.0;
     const double2 moff = make_double2(-rc.off.x, -rc.off.y);  // -e
+    // -e v and d - e^2 v; e is real in SPEC launches
+    auto mul_moff = [&](double2 v) { return SPEC ? cscale(v, moff.x) : cmul(moff, v); };
+    auto sub_off2 = [&](double2 v, double2 d) {
+      return SPEC ? make_double2(fma(-rc.off2.x, v.x, d.x), fma(-rc.off2.x, v.y, d.y)) : cfms(rc.off2, v, d);
+    };
     double2 z[C];
 #pragma unroll
     for (int j = 0; j < C; ++j) z[j] = has_row(j) ? S[slot_of(j)] : make_double2(0, 0);
@@ -651,12 +667,12 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     if (XR && last && valid) {
       const int x = nL - 1;
       if (a.in) xrhs = to_d2(reinterpret_cast<const T*>(a.in)[loff + x]);
-      if (a.PO) {
+      if (RANK2 && a.PO) {
         const T* po = reinterpret_cast<const T*>(a.PO) + (int64_t)(b * 2) * a.nI * nL + (int64_t)m * nL;
         xrhs = cfma(a.alpha0[l], to_d2(po[x]), xrhs);
         xrhs = cfma(a.alpha1[l], to_d2(po[(int64_t)a.nI * nL + x]), xrhs);
       }
-      if (a.PI) {
+      if (RANK2 && a.PI) {
         const T* pi = reinterpret_cast<const T*>(a.PI) + (int64_t)((b * a.nO + l) * 2) * nL;
         xrhs = cfma(a.beta0[m], to_d2(pi[x]), xrhs);
         xrhs = cfma(a.beta1[m], to_d2(pi[nL + x]), xrhs);
@@ -676,12 +692,12 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         if (has_row(j)) {
-          const double2 f = cmul(moff, ipp);
+          const double2 f = mul_moff(ipp);
           A.f = cmul(f, A.f);
           A.g = cfma(f, A.g, z[j]);
           const bool end = !XR && q == P - 1 && (j == C - 1 || (BAL && j == C - 2 && !full));
           double2 pv = (j == 0 && q == 0) ? rc.dlo : (end ? rc.dhi : rc.dint);
-          pv = cfms(rc.off2, ipp, pv);  // ipp = 0 at x = 0
+          pv = sub_off2(ipp, pv);  // ipp = 0 at x = 0
           ipp = crcp_fast(pv);
           S[slot_of(j)] = ipp;
         }
@@ -696,21 +712,21 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     double2 yx = make_double2(0, 0);  // y of the extra row (XR, last lane)
     {
       double2 zp = Ein.g;
-      double2 mp = cmul(moff, ip_in);
+      double2 mp = mul_moff(ip_in);
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         if (has_row(j)) {
           zp = cfma(mp, zp, z[j]);
           const double2 ipj = S[slot_of(j)];
           z[j] = cmul(zp, ipj);
-          mp = cmul(moff, ipj);
+          mp = mul_moff(ipj);
           S[slot_of(j)] = mp;
         }
       }
       if (XR && last) {
         // extra row: w = r + (-e / p_{nL-2}) w_{nL-2}, p = d_hi - e^2 / p_{nL-2}
-        const double2 wx = cfma(cmul(moff, ipp_last), zp, xrhs);
-        yx = cmul(wx, crcp_fast(cfms(rc.off2, ipp_last, rc.dhi)));
+        const double2 wx = cfma(mul_moff(ipp_last), zp, xrhs);
+        yx = cmul(wx, crcp_fast(sub_off2(ipp_last, rc.dhi)));
       }
     }
 
@@ -762,14 +778,14 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     if constexpr (RED) {
       if (valid) {
         const uint32_t wi = (a.red == 1) ? m : l;
-        const double2 w0 = EARLY ? ew0 : a.rho0[wi], w1 = EARLY ? ew1 : a.rho1[wi];
+        const double2 w0 = EARLY ? ew0 : (SPEC ? make_double2(0, 0) : a.rho0[wi]), w1 = EARLY ? ew1 : a.rho1[wi];
         if (XR && last) {
-          accx0 = cfma(w0, yx, accx0);
+          accx0 = SPEC ? cadd(yx, accx0) : cfma(w0, yx, accx0);
           accx1 = cfma(w1, yx, accx1);
         }
 #pragma unroll
         for (int j = 0; j < C; ++j) {  // (a missing row holds zero)
-          acc0[j] = cfma(w0, z[j], acc0[j]);
+          acc0[j] = SPEC ? cadd(z[j], acc0[j]) : cfma(w0, z[j], acc0[j]);
           acc1[j] = cfma(w1, z[j], acc1[j]);
         }
       }
@@ -779,6 +795,14 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
   // ---- cross-slot reduction (fixed slot order) and partial write -----------
   if constexpr (RED) {
     double2* outp = a.part + ((int64_t)g * a.ntiles + t) * 2 * nL;
+    // SPEC: rho_0 is the same real number for every mode (1/n of a periodic
+    // axis), applied here to the plain sums
+    const double sc0 = SPEC ? a.rho0[0].x : 1.0;
+    if constexpr (SPEC) {
+#pragma unroll
+      for (int j = 0; j < C; ++j) acc0[j] = cscale(acc0[j], sc0);
+      accx0 = cscale(accx0, sc0);
+    }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       __syncthreads();
@@ -819,56 +843,56 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
   }
 }
 
-template <typename T, int NT, int P, int C, bool RED, bool XR, bool BAL>
+template <typename T, int NT, int P, int C, bool RED, bool XR, bool BAL, bool SPEC>
 hipError_t launch_R(const LineDev& d, int64_t blocks, hipStream_t s) {
   // staging areas: up to 72 KB at NT = 512, above the default dynamic LDS
   // limit, so raise the limit for this kernel once
   static bool attr = false;
   constexpr int lds = (NT / 64) * 72 * C * (int)sizeof(double2);
   if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lines_kernel<T, NT, P, C, RED, XR, BAL>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lines_kernel<T, NT, P, C, RED, XR, BAL, SPEC>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     attr = true;
   }
-  hipLaunchKernelGGL((lines_kernel<T, NT, P, C, RED, XR, BAL>), dim3((unsigned)blocks), dim3(NT), lds, s, d);
+  hipLaunchKernelGGL((lines_kernel<T, NT, P, C, RED, XR, BAL, SPEC>), dim3((unsigned)blocks), dim3(NT), lds, s, d);
   return hipGetLastError();
 }
 
 // The kernel of a geometry (lines_geometry): exact lines, lines with the extra
 // row, or balanced chunks of c and c - 1 rows.
-template <typename T, bool RED, int NT, int P>
+template <typename T, bool RED, bool SPEC, int NT, int P>
 hipError_t launch_P(const LineDev& d, int64_t blocks, hipStream_t s) {
-  if (d.nL == P * 8) return launch_R<T, NT, P, 8, RED, false, false>(d, blocks, s);
+  if (d.nL == P * 8) return launch_R<T, NT, P, 8, RED, false, false, SPEC>(d, blocks, s);
   if constexpr (P >= 64) {
-    if (d.nL == P * 8 + 1) return launch_R<T, NT, P, 8, RED, true, false>(d, blocks, s);
+    if (d.nL == P * 8 + 1) return launch_R<T, NT, P, 8, RED, true, false, SPEC>(d, blocks, s);
   }
   if (d.r < 0 || d.r > P || d.nL != P * (d.c - 1) + d.r) return hipErrorInvalidValue;
   switch (d.c) {
     case 4:
-      if constexpr (P == 1) return launch_R<T, NT, P, 4, RED, false, true>(d, blocks, s);
+      if constexpr (P == 1) return launch_R<T, NT, P, 4, RED, false, true, SPEC>(d, blocks, s);
       return hipErrorInvalidValue;
-    case 5: return launch_R<T, NT, P, 5, RED, false, true>(d, blocks, s);
-    case 6: return launch_R<T, NT, P, 6, RED, false, true>(d, blocks, s);
-    case 7: return launch_R<T, NT, P, 7, RED, false, true>(d, blocks, s);
-    case 8: return launch_R<T, NT, P, 8, RED, false, true>(d, blocks, s);
+    case 5: return launch_R<T, NT, P, 5, RED, false, true, SPEC>(d, blocks, s);
+    case 6: return launch_R<T, NT, P, 6, RED, false, true, SPEC>(d, blocks, s);
+    case 7: return launch_R<T, NT, P, 7, RED, false, true, SPEC>(d, blocks, s);
+    case 8: return launch_R<T, NT, P, 8, RED, false, true, SPEC>(d, blocks, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <typename T, bool RED>
+template <typename T, bool RED, bool SPEC>
 hipError_t launch_lines_kernel(const LineDev& d, int P, int64_t blocks, hipStream_t s) {
   switch (P) {
-    case 1: return launch_P<T, RED, 256, 1>(d, blocks, s);
-    case 2: return launch_P<T, RED, 256, 2>(d, blocks, s);
-    case 4: return launch_P<T, RED, 256, 4>(d, blocks, s);
-    case 8: return launch_P<T, RED, 256, 8>(d, blocks, s);
-    case 16: return launch_P<T, RED, 256, 16>(d, blocks, s);
-    case 32: return launch_P<T, RED, 256, 32>(d, blocks, s);
-    case 64: return launch_P<T, RED, 256, 64>(d, blocks, s);
-    case 128: return launch_P<T, RED, 256, 128>(d, blocks, s);
-    case 256: return launch_P<T, RED, 256, 256>(d, blocks, s);
-    case 512: return launch_P<T, RED, 512, 512>(d, blocks, s);
+    case 1: return launch_P<T, RED, SPEC, 256, 1>(d, blocks, s);
+    case 2: return launch_P<T, RED, SPEC, 256, 2>(d, blocks, s);
+    case 4: return launch_P<T, RED, SPEC, 256, 4>(d, blocks, s);
+    case 8: return launch_P<T, RED, SPEC, 256, 8>(d, blocks, s);
+    case 16: return launch_P<T, RED, SPEC, 256, 16>(d, blocks, s);
+    case 32: return launch_P<T, RED, SPEC, 256, 32>(d, blocks, s);
+    case 64: return launch_P<T, RED, SPEC, 256, 64>(d, blocks, s);
+    case 128: return launch_P<T, RED, SPEC, 256, 128>(d, blocks, s);
+    case 256: return launch_P<T, RED, SPEC, 256, 256>(d, blocks, s);
+    case 512: return launch_P<T, RED, SPEC, 512, 512>(d, blocks, s);
     default: return hipErrorInvalidValue;
   }
 }

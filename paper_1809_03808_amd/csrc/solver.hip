@@ -881,6 +881,7 @@ int inner_solve(helm_plan* p, const Level& lv, const InnerIO& io, hipStream_t st
   base.kHi = p->kHi;
   base.piv = io.seedB;
   base.sTab = io.sigTB;
+  base.real_sigma = io.sigTB == p->sig[0];
   double2* part = p->part.as<double2>();
   const double elems = (double)lv.nb * lv.nO * lv.nI * lv.nL;
   int tile, nt;
@@ -927,6 +928,7 @@ int inner_solve(helm_plan* p, const Level& lv, const InnerIO& io, hipStream_t st
   s2.sI = I.sigA;
   s2.piv = io.seedA;
   s2.sTab = io.sigTA;
+  s2.real_sigma = false;
   s2.PI = p->PIb.p;  // complex128: the launch has no line storage
   s2.r2_kind = ST_C128;
   s2.beta0 = I.va0d;
@@ -1206,6 +1208,7 @@ int solve_modal(helm_plan* p, const Level& lv, int kind, hipStream_t st) {
   base.kHi = p->kHi;
   base.piv = p->seed[0];
   base.sTab = p->sig[0];
+  base.real_sigma = true;
   base.in = p->W0.p;
   base.in_kind = kind;
   base.r2_kind = kind;
