@@ -771,36 +771,47 @@ int run_fft(helm_plan* p, const PAxis& a, int sign, bool fp32, const void* in, i
 int red_l_mode(const helm_plan* p) { return p->red_layout; }
 
 // Lines per tile and tiles of a line launch; `layout` (2 or 3) only matters
-// for red 2.  At least 8 lines feed each partial sum (partials stay below 1/4
-// of an N-sized array).  A reducing launch writes one partial of 2 nL values
-// per block, so it uses about as many blocks as stay resident at once (one
-// 512-thread or two 256-thread blocks per compute unit at the register use of
-// the reducing kernels) and no more; other launches take up to 2048 blocks.
-// Layout 3 writes one partial per slot and splits the l of every group of
-// consecutive m into as few tiles as give at least 1024 blocks.
+// for red 2.  At least 8 lines feed each partial sum of layouts 1 and 2
+// (partials stay below 1/4 of an N-sized array).  A reducing launch writes one
+// partial of 2 nL values per block (layout 3: per slot), and R blocks stay
+// resident at once (one 512-thread or two 256-thread blocks per compute unit at
+// the register use of the reducing kernels), so its tiles are those that take
+// the fewest iterations in rounds of R blocks, a block's start and partials
+// counted as 0.7 of an iteration: 512 blocks at 256^3, and not the 516 that
+// left four blocks to a second round at 129^3 x 2 (70 us; 774 blocks of two
+// thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us).
+// Other launches take up to 2048 blocks.
 void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, int* tile, int* ntiles) {
   int P, c, NT;
   lines_geometry(nL, &P, &c, &NT);
   const int LPB = NT / P;
-  if (red == 2 && layout == 3) {
-    const int64_t groups = (int64_t)nb * ((nI + LPB - 1) / LPB);
-    int64_t nt = groups >= 1024 ? 1 : (1024 + groups - 1) / groups;
-    if (nt > nO) nt = nO;
-    const int64_t t = (nO + nt - 1) / nt;
+  if (red == 0) {
+    const int64_t lines = (int64_t)nb * nO * nI;
+    int64_t t = LPB;
+    if (lines / t > 2048) t = (lines + 2047) / 2048;
+    t = (t + LPB - 1) / LPB * LPB;
     *tile = (int)t;
-    *ntiles = (int)((nO + t - 1) / t);
+    *ntiles = (int)((lines + t - 1) / t);
     return;
   }
-  const int64_t extent = red == 1 ? nI : (red == 2 ? nO : (int64_t)nb * nO * nI);
-  const int64_t groups = red == 1 ? (int64_t)nb * nO : (red == 2 ? (int64_t)nb * nI : 1);
-  int64_t t = red ? 8 : LPB;
-  const int64_t lines = extent * groups;
-  const int64_t target = red ? (NT >= 512 ? 256 : 512) : 2048;
-  if (lines / t > target) t = (lines + target - 1) / target;
-  if (red && t > extent) t = extent;
-  t = (t + LPB - 1) / LPB * LPB;
-  *tile = (int)t;
-  *ntiles = (int)((extent + t - 1) / t);
+  const bool l3 = red == 2 && layout == 3;
+  const int64_t R = NT >= 512 ? 256 : 512;
+  const int64_t extent = red == 1 ? nI : nO;
+  const int64_t groups = (int64_t)nb * (red == 1 ? nO : (l3 ? (nI + LPB - 1) / LPB : nI));
+  // lines per iteration of a block along the reduced index, and per tile
+  const int64_t step = l3 ? 1 : LPB, tmin = l3 ? 1 : std::min<int64_t>(8, extent);
+  double best = 1e300;
+  for (int64_t n = 1; n <= extent && (n == 1 || groups * n <= 8 * R); ++n) {
+    int64_t t = std::max((extent + n - 1) / n, tmin);
+    t = (t + step - 1) / step * step;
+    const int64_t nt = (extent + t - 1) / t;
+    const double cost = (double)((groups * nt + R - 1) / R) * ((double)(t / step) + 0.7);
+    if (cost < 0.98 * best) {
+      best = cost;
+      *tile = (int)t;
+      *ntiles = (int)nt;
+    }
+  }
 }
 
 void tiles_for(const helm_plan* p, int red, int nb, int nO, int nI, int nL, int* tile, int* ntiles) {
