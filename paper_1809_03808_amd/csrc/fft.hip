@@ -161,6 +161,7 @@ struct PassDev {
   const void* cin;
   const void* cout;
   int64_t chirp_n, chirp_na, chirp_S;
+  int64_t cq;  // col / chirp_S of the thread (0 in a one-pass convolution)
   int tw4_mode, conj_out;
   int64_t I, od, in_so, in_sj, out_so1, out_so2, out_sk, tw4_S;
   int64_t ntile;  // tiles along I
@@ -253,47 +254,77 @@ template <int W, typename C> __device__ inline int64_t tile_of_block(int64_t b, 
 // place in LDS.  The first stage reads global memory, the last writes it
 // (with the four-step twiddle, the per-mode scale and the optional
 // accumulation).
+// What a stage loads from memory besides the data (the roots, and in the last
+// forward stage of a convolution the transformed kernel) is loaded before the
+// LDS reads and the barrier, so that its latency passes during them; row
+// addresses advance by uniform strides from one 64-bit product per butterfly.
 template <int L, int W, int NT, int R, int Ns, bool FIRST, bool LAST, typename C, bool GIN = true, bool GOUT = true,
           bool REG = false>
 __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out, int64_t o, int64_t i0,
                              int64_t oq, int64_t orr, int64_t a4, const C* vin, int tid) {
   constexpr bool LOADG = FIRST && GIN;    // this stage reads global memory
   constexpr bool STOREG = LAST && GOUT;   // this stage writes global memory
+  constexpr bool KERN = LAST && !GOUT;    // end of a convolution's forward transform
   constexpr int LR = L / R;
   constexpr int NBF = LR * W;
   static_assert(NT % W == 0 && lds_elems<L, W, C>() * (int)sizeof(C) <= 160 * 1024, "tile does not fit the thread block or LDS");
   constexpr int NB = (NBF + NT - 1) / NT;
+  constexpr int step = L / (Ns * R);
   const int w = tid % W;
   const int64_t col = i0 + w;
   const bool colok = col < p.I;
   const C* tw = reinterpret_cast<const C*>(p.tw);
-  C v[NB][R];
+  C v[NB][R], tv[NB][R], hv[KERN ? NB : 1][KERN ? R : 1];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    const int t = tid + q * NT;
+    if (NB * NT == NBF || t < NBF) {
+      const int j = t / W, k = j % Ns;
+      if constexpr (Ns > 1) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) tv[q][r] = tw[r * k * step];
+      }
+      if constexpr (KERN) {
+        const C* hk = reinterpret_cast<const C*>(p.cmode) + orr + p.od * ((j / Ns) * Ns * R + k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) hv[q][r] = hk[p.od * (r * Ns)];
+      }
+    }
+  }
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
     const int t = tid + q * NT;
     if (NB * NT == NBF || t < NBF) {
       const int j = t / W;
+      if constexpr (LOADG && REG) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int row = j + r * LR;
-        if constexpr (LOADG && REG) {
-          v[q][r] = vin[q * R + r];  // loaded by the caller
-        } else if constexpr (LOADG) {
-          C x;
-          x.x = 0;
-          x.y = 0;
-          if (p.cin) {
-            const int64_t xr = col / p.chirp_S + p.chirp_na * row;
-            if (colok && xr < p.chirp_n)
-              x = cmul(load_as<C>(in, o * p.in_so + (int64_t)row * p.in_sj + col, p.in_kind),
-                       reinterpret_cast<const C*>(p.cin)[xr]);
-          } else if (colok) {
-            x = load_as<C>(in, o * p.in_so + (int64_t)row * p.in_sj + col, p.in_kind);
+        for (int r = 0; r < R; ++r) v[q][r] = vin[q * R + r];  // loaded by the caller
+      } else if constexpr (LOADG) {
+        const int64_t off = o * p.in_so + (int64_t)j * p.in_sj + col, rs = LR * p.in_sj;
+        if (p.cin) {
+          const int64_t xr = p.cq + p.chirp_na * j, xs = p.chirp_na * LR;
+          const C* ci = reinterpret_cast<const C*>(p.cin) + xr;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            C x;
+            x.x = 0;
+            x.y = 0;
+            if (colok && xr + r * xs < p.chirp_n) x = cmul(load_as<C>(in, off + r * rs, p.in_kind), ci[r * xs]);
+            v[q][r] = x;
           }
-          v[q][r] = x;
         } else {
-          v[q][r] = sm[lpos<W, C>(row, w)];
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            C x;
+            x.x = 0;
+            x.y = 0;
+            if (colok) x = load_as<C>(in, off + r * rs, p.in_kind);
+            v[q][r] = x;
+          }
         }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[q][r] = sm[lpos<W, C>(j + r * LR, w)];
       }
     }
   }
@@ -305,17 +336,27 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
       const int j = t / W;
       const int k = j % Ns;
       if constexpr (Ns > 1) {
-        constexpr int step = L / (Ns * R);
 #pragma unroll
-        for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], tw[r * k * step]);
+        for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], tv[q][r]);
       }
       dft<R, C>(v[q], p.sign);
       const int base = (j / Ns) * Ns * R + k;
       if constexpr (!STOREG) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) sm[lpos<W, C>(base + r * Ns, w)] = v[q][r];
+        for (int r = 0; r < R; ++r) {
+          if constexpr (KERN) {
+            v[q][r] = cmul(v[q][r], hv[q][r]);
+            v[q][r].y = -v[q][r].y;
+          }
+          sm[lpos<W, C>(base + r * Ns, w)] = v[q][r];
+        }
       } else {
         if (colok) {
+          const int64_t oi0 = oq * p.out_so1 + orr * p.out_so2 + (int64_t)base * p.out_sk + col, os = Ns * p.out_sk;
+          // mode index of the per-mode factors: the chirp row map when folding
+          // a chirp, else the pass's own output index
+          const int64_t mi0 = p.cout ? p.cq + p.chirp_na * base : orr + p.od * base;
+          const int64_t ms = (p.cout ? p.chirp_na : p.od) * Ns;
           // Accumulating over 1024 and more points, one block of 1024 threads
           // per compute unit: all old values are loaded before the first
           // store (a store may alias the next load, so loads between the
@@ -329,22 +370,15 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
           if (EARLY && early) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-              const int kk = base + r * Ns;
-              const bool ok = !p.cout || col / p.chirp_S + p.chirp_na * kk < p.chirp_n;
-              const int64_t oi = oq * p.out_so1 + orr * p.out_so2 + kk * p.out_sk + col;
-              old[EARLY ? r : 0] = ok ? reinterpret_cast<const double2*>(out)[oi] : make_double2(0, 0);
+              const bool ok = !p.cout || mi0 + r * ms < p.chirp_n;
+              old[EARLY ? r : 0] = ok ? reinterpret_cast<const double2*>(out)[oi0 + r * os] : make_double2(0, 0);
             }
           }
 #pragma unroll
           for (int r = 0; r < R; ++r) {
             const int kk = base + r * Ns;  // output frequency of this pass
-            // mode index of the per-mode factors: the chirp row map when
-            // folding a chirp, else the pass's own output index
-            int64_t mi = orr + p.od * kk;
-            if (p.cout) {
-              mi = col / p.chirp_S + p.chirp_na * kk;
-              if (mi >= p.chirp_n) continue;  // rows past the transform length are not stored
-            }
+            const int64_t mi = mi0 + r * ms, oi = oi0 + r * os;
+            if (p.cout && mi >= p.chirp_n) continue;  // rows past the transform length are not stored
             C y = v[q][r];
             if (p.conj_out) y.y = -y.y;
             if (p.tw4) {
@@ -358,9 +392,9 @@ __device__ inline void stage(const PassDev& p, C* sm, const void* in, void* out,
             if (p.scale) s *= p.scale[mi];
             y.x = (typename RealOf<C>::T)(y.x * s);
             y.y = (typename RealOf<C>::T)(y.y * s);
-            const int64_t oi = oq * p.out_so1 + orr * p.out_so2 + kk * p.out_sk + col;
             if (EARLY && early)
-              reinterpret_cast<double2*>(out)[oi] = make_double2((double)y.x + old[EARLY ? r : 0].x, (double)y.y + old[EARLY ? r : 0].y);
+              reinterpret_cast<double2*>(out)[oi] =
+                  make_double2((double)y.x + old[EARLY ? r : 0].x, (double)y.y + old[EARLY ? r : 0].y);
             else
               store_as<C>(out, oi, p.out_kind, y, p.acc);
           }
@@ -383,18 +417,41 @@ __device__ inline void stages(const PassDev& p, C* sm, const void* in, void* out
   }
 }
 
-template <int L, typename C, int WO = 0>
-__global__ __launch_bounds__((threads_for<L, WO>()), (min_waves_of<L, C, WO>())) void fft_pass_kernel(PassDev p,
+// Quotient of a column by a positive 64-bit divisor: 32-bit where it fits (a
+// 64-bit division is about a hundred instructions).
+__device__ inline int64_t col_div(int64_t col, int64_t d) {
+  if ((uint64_t)col >> 32 || (uint64_t)d >> 32) return col / d;
+  return (uint32_t)col / (uint32_t)d;
+}
+
+// PLAIN: a single pass of a power-of-two axis, without chirp, four-step twiddle
+// or per-mode complex factor (checked by the launcher and set here as
+// constants, so that no stage carries their branches).
+template <int L, typename C, int WO, bool PLAIN>
+__global__ __launch_bounds__((threads_for<L, WO>()), (min_waves_of<L, C, WO>())) void fft_pass_kernel(PassDev p0,
                                                                                                      const void* in,
                                                                                                      void* out) {
   constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
   __shared__ C sm[nstages(L) > 1 ? lds_elems<L, W, C>() : 1];
-  if (p.skip && *p.skip) return;
-  const int64_t blk = tile_of_block<W, C>(blockIdx.x, gridDim.x);
-  const int64_t o = blk / p.ntile;
-  const int64_t i0 = (blk - o * p.ntile) * W;
-  const int64_t oq = o / p.od, orr = o - oq * p.od;
-  const int64_t a4 = p.tw4 ? (i0 + (int64_t)(threadIdx.x % W)) / p.tw4_S : 0;
+  if (p0.skip && *p0.skip) return;
+  PassDev p = p0;
+  const uint32_t blk = (uint32_t)tile_of_block<W, C>(blockIdx.x, gridDim.x), nt = (uint32_t)p.ntile;
+  const uint32_t o = blk / nt;
+  const int64_t i0 = (int64_t)(blk - o * nt) * W;
+  const int64_t col = i0 + (int64_t)(threadIdx.x % W);
+  int64_t oq = o, orr = 0, a4 = 0;
+  if constexpr (PLAIN) {
+    p.cin = p.cout = p.cmode = p.tw4 = nullptr;
+    p.conj_out = 0;
+    p.od = 1;
+  } else {
+    if (p.od > 1) {
+      oq = o / (uint32_t)p.od;
+      orr = o - oq * p.od;
+    }
+    if (p.tw4 && !p.tw4_mode) a4 = col_div(col, p.tw4_S);
+    if (p.cin || p.cout) p.cq = col_div(col, p.chirp_S);
+  }
   stages<L, W, NT, 0, 1, C>(p, sm, in, out, o, i0, oq, orr, a4);
 }
 
@@ -500,33 +557,35 @@ __global__ __launch_bounds__(threads_of(L), 1) void fft_stream_kernel(PassDev p0
 }
 
 // Chirp-z middle pass: forward DFT over the rows into LDS, multiplication by
-// the transformed kernel, conjugation, a second forward DFT, and the
-// conjugating epilogue: conj(DFT(conj(X))) is the unscaled inverse DFT.
-// With L the whole convolution length and the chirps folded into the first
-// load and the last store, it is the complete transform in one pass.
-template <int L, typename C, int WO = 0>
-__global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassDev p, const void* in, void* out) {
+// the transformed kernel and conjugation as its last stage writes them, a
+// second forward DFT, and the conjugating epilogue: conj(DFT(conj(X))) is the
+// unscaled inverse DFT.  ONE: L is the whole convolution length and the chirps
+// are folded into the first load and the last store, so that the pass is the
+// complete transform.
+template <int L, typename C, int WO, bool ONE>
+__global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassDev p0, const void* in, void* out) {
   constexpr int W = tile_w_of<L, C, WO>(), NT = threads_for<L, WO>();
   __shared__ C sm[lds_elems<L, W, C>()];
-  if (p.skip && *p.skip) return;
-  const int64_t blk = tile_of_block<W, C>(blockIdx.x, gridDim.x);
-  const int64_t o = blk / p.ntile;
-  const int64_t i0 = (blk - o * p.ntile) * W;
-  const int64_t oq = o / p.od, orr = o - oq * p.od;
-  stages<L, W, NT, 0, 1, C, true, false>(p, sm, in, out, o, i0, oq, orr, 0);
-  const C* hk = reinterpret_cast<const C*>(p.cmode);
-  for (int e = threadIdx.x; e < L * W; e += NT) {
-    const int d = e / W;
-    C& z = sm[lpos<W, C>(d, e % W)];
-    C y = cmul(z, hk[orr + p.od * d]);
-    y.y = -y.y;
-    z = y;
+  if (p0.skip && *p0.skip) return;
+  PassDev p = p0;
+  const uint32_t blk = (uint32_t)tile_of_block<W, C>(blockIdx.x, gridDim.x), nt = (uint32_t)p.ntile;
+  const uint32_t o = blk / nt;
+  const int64_t i0 = (int64_t)(blk - o * nt) * W;
+  int64_t oq = o, orr = 0;
+  if constexpr (ONE) {
+    p.od = 1;
+    p.chirp_na = 1;
+    p.tw4 = nullptr;
+  } else {
+    p.cin = p.cout = nullptr;
+    if (p.od > 1) {
+      oq = o / (uint32_t)p.od;
+      orr = o - oq * p.od;
+    }
   }
-  __syncthreads();
-  PassDev q = p;
-  q.cmode = nullptr;
-  q.cin = nullptr;
-  stages<L, W, NT, 0, 1, C, false, true>(q, sm, in, out, o, i0, oq, orr, 0);
+  stages<L, W, NT, 0, 1, C, true, false>(p, sm, in, out, o, i0, oq, orr, 0);
+  p.cmode = nullptr;
+  stages<L, W, NT, 0, 1, C, false, true>(p, sm, in, out, o, i0, oq, orr, 0);
 }
 
 // Compute units of the current device.  (Cached per device; threads that race
@@ -561,8 +620,16 @@ hipError_t launch_conv_L(const PassDev& p, int64_t O, const void* in, void* out,
   const int64_t blocks = O * q.ntile;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((conv_pass_kernel<L, C, WO>), dim3((unsigned)blocks), dim3((threads_for<L, WO>())), 0, s, q, in,
-                     out);
+  const dim3 g((unsigned)blocks), b(threads_for<L, WO>());
+  if (p.cin && p.cout && !p.tw4 && p.od == 1 && p.chirp_na == 1 && p.chirp_S >= p.I) {
+    hipLaunchKernelGGL((conv_pass_kernel<L, C, WO, true>), g, b, 0, s, q, in, out);
+  } else {
+    if constexpr (L > 512) return hipErrorInvalidValue;  // middle passes are at most 512 rows long
+    else {
+      if (p.cin || p.cout) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((conv_pass_kernel<L, C, WO, false>), g, b, 0, s, q, in, out);
+    }
+  }
   return hipGetLastError();
 }
 
@@ -607,8 +674,13 @@ hipError_t launch_L(const PassDev& p, int64_t O, const void* in, void* out, hipS
   const int64_t blocks = O * q.ntile;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fft_pass_kernel<L, C, WO>), dim3((unsigned)blocks), dim3((threads_for<L, WO>())), 0, s, q, in,
-                     out);
+  const dim3 g((unsigned)blocks), b(threads_for<L, WO>());
+  if (!p.cin && !p.cout && !p.cmode && !p.tw4 && !p.conj_out && p.od == 1)
+    hipLaunchKernelGGL((fft_pass_kernel<L, C, WO, true>), g, b, 0, s, q, in, out);
+  else if constexpr (L <= 512)
+    hipLaunchKernelGGL((fft_pass_kernel<L, C, WO, false>), g, b, 0, s, q, in, out);
+  else
+    return hipErrorInvalidValue;  // single passes of power-of-two axes only
   return hipGetLastError();
 }
 
@@ -706,6 +778,7 @@ static PassDev make_pass_dev(const FftPass& f) {
   p.chirp_S = f.chirp_S > 0 ? f.chirp_S : 1;
   p.tw4_mode = f.tw4_mode;
   p.conj_out = f.conj_out;
+  p.cq = 0;
   p.ntile = 0;
   return p;
 }

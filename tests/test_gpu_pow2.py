@@ -22,7 +22,7 @@ def test_pow2_forms(grid, prec, tmp_path):
     f = inputs.gaussian_batch(grid, [51, 52])
     ref = fem.solve(grid, h, omega, abc, f.reshape(2, -1))
     key = f"dim={dim} grid={grid[0]}x{grid[1]}x{grid[2] if dim == 3 else 1} prec={prec}"
-    axis = int(np.argmax(grid))
+    axis = int(np.argmax(grid[:-1]))
     cache = tmp_path / "tune.txt"
     with helm.Plan(grid, h, omega, precision=prec, tune_cache=str(cache)):
         pass
@@ -39,3 +39,27 @@ def test_pow2_forms(grid, prec, tmp_path):
         assert rc in (helm.HELM_OK, helm.HELM_ENOCONV)
         assert len([ln for ln in forced.read_text().splitlines() if " pow2" in ln]) == 1
         assert np.max(fem.rel_error(u, ref)) <= 1e-9
+
+
+@pytest.mark.parametrize("prec", [helm.PREC_FP64, helm.PREC_MIXED])
+@pytest.mark.parametrize("grid", [(1024, 4095), (2048, 2300), (4096, 1043)])
+def test_single_passes_of_many_tiles(grid, prec, tmp_path):
+    """More tiles than compute units, the last ones ragged: both tiles of the
+    single pass against two passes, each refined twice."""
+    h = (1.0 / (max(grid) - 1),) * 2
+    omega = 2 * np.pi * (max(grid) - 1) / 10
+    key = f"dim=2 grid={grid[0]}x{grid[1]}x1 prec={prec}"
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    f = torch.view_as_complex(torch.randn((1,) + grid + (2,), generator=g, device="cuda", dtype=torch.float64))
+    out = []
+    for choice in (0, 1, 2):
+        cache = tmp_path / f"forced{choice}.txt"
+        cache.write_text(f"helm-tune {key} pow20={choice}\n")
+        with helm.Plan(grid, h, omega, precision=prec, tol=0.0, max_iter=2, tune_cache=str(cache)) as plan:
+            u = torch.empty_like(f)
+            plan.solve(f, u, raise_on_error=False)
+            assert plan.report()["rel_residual_max"] <= 1e-10
+        out.append(u)
+    for u in out[1:]:
+        assert (torch.linalg.vector_norm(u - out[0]) / torch.linalg.vector_norm(out[0])).item() <= 1e-9
