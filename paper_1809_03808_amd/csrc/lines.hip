@@ -143,6 +143,7 @@ hipError_t launch_lines(LineArgs a, hipStream_t s) {
     // storing launches over (outer, inner) mode tiles: the rank-2 rows of an
     // inner mode (PO) are then read again only once per outer tile, those of
     // an outer mode (PI) once per inner tile
+    if (a.tile_l < 1 || (a.tile_m & (a.tile_m - 1))) return hipErrorInvalidValue;
     d.tl = a.tile_l;
     d.tm = a.tile_m;
     d.tile = a.tile_l * a.tile_m;

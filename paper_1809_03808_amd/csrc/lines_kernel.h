@@ -310,55 +310,97 @@ __host__ __device__ inline int chunk_start(int q, int c, int r) { return q * (c 
 // e(x) = coupling between rows x-1 and x
 __device__ inline bool has_e(int x, int nL) { return x > 0 && x < nL; }
 
-// Line index (b, l, m) of slot `sl` of tile t at iteration `it`; false past
-// the end of the tile's extent.  Line counts stay below 2^31 (checked at
-// launch), so 32-bit index arithmetic suffices.  Reductions over l come in
-// two layouts: red 2 gives a block one m and its slots consecutive l (lines
-// nI nL elements apart); red 3 gives the slots of a block lpb consecutive m
-// at one l per iteration, so one iteration reads lpb adjacent lines and the
-// rows PI[b][l] once, and every slot keeps its own partial sum.
-__device__ inline bool decode_line(const LineDev& a, uint32_t g, uint32_t t, int lpb, int it, int sl,
-                                   uint32_t& b, uint32_t& l, uint32_t& m) {
-  const uint32_t li = a.red == 3 ? t * (uint32_t)a.tile + (uint32_t)it
-                                 : t * (uint32_t)a.tile + (uint32_t)(it * lpb + sl);
-  const uint32_t nO = a.nO, nI = a.nI;
-  bool valid;
-  if (a.red == 1) {        // g = b*nO + l, li = m
-    valid = li < nI;
-    b = g / nO;
-    l = g - b * nO;
-    m = li;
-  } else if (a.red == 2) { // g = b*nI + m, li = l
-    valid = li < nO;
-    b = g / nI;
-    m = g - b * nI;
-    l = li;
-  } else if (a.red == 3) { // g = b*nmg + mg, li = l, m = mg*lpb + sl
-    const uint32_t nmg = (nI + (uint32_t)lpb - 1) / (uint32_t)lpb;
-    b = g / nmg;
-    m = (g - b * nmg) * (uint32_t)lpb + (uint32_t)sl;
-    l = li;
-    valid = li < nO && m < nI;
-  } else if (a.tm > 0) {   // tile t = (b, mt, lt), li - t*tile = (l - lt*tl)*tm + (m - mt*tm)
-    const uint32_t nlt = (nO + (uint32_t)a.tl - 1) / (uint32_t)a.tl, nmt = (nI + (uint32_t)a.tm - 1) / (uint32_t)a.tm;
-    const uint32_t idx = li - t * (uint32_t)a.tile;
-    const uint32_t bm = t / nlt, lt = t - bm * nlt;
-    b = bm / nmt;
-    const uint32_t mt = bm - b * nmt;
-    const uint32_t il = idx / (uint32_t)a.tm;
-    l = lt * (uint32_t)a.tl + il;
-    m = mt * (uint32_t)a.tm + (idx - il * (uint32_t)a.tm);
-    valid = idx < (uint32_t)a.tile && l < nO && m < nI && b < (uint32_t)a.nb;
-  } else {                 // li = (b*nO + l)*nI + m
-    valid = li < (uint32_t)a.nb * nO * nI;
-    const uint32_t bl = li / nI;
-    m = li - bl * nI;
-    b = bl / nO;
-    l = bl - b * nO;
+// The lines of a block.  Line index (b, l, m) of slot `sl` at iteration `it`;
+// false past the end of the tile's extent.  Line counts stay below 2^31 (checked
+// at launch), so 32-bit index arithmetic suffices; the divisions (about thirty
+// instructions each, against some four hundred of a whole 8-row chunk) are made
+// once per block.  Reductions over l come in two layouts: red 2 gives a block
+// one m and its slots consecutive l (lines nI nL elements apart); red 3 gives
+// the slots of a block lpb consecutive m at one l per iteration, so one
+// iteration reads lpb adjacent lines and the rows PI[b][l] once, and every slot
+// keeps its own partial sum.  Storing launches take tiles of tl outer x tm inner
+// modes (tm a power of two), or consecutive lines.
+template <bool RED> struct BlockLines {
+  uint32_t b, l, m;  // line of iteration 0, slot 0
+  uint32_t first;    // consecutive storing launches: its index
+  uint32_t tmsh;     // tiled ones: log2 tm
+
+  __device__ BlockLines(const LineDev& a, uint32_t g, uint32_t t, uint32_t lpb) {
+    const uint32_t nO = a.nO, nI = a.nI, base = t * (uint32_t)a.tile;
+    first = tmsh = 0;
+    if constexpr (RED) {
+      if (a.red == 1) {         // g = b*nO + l
+        b = g / nO;
+        l = g - b * nO;
+        m = base;
+      } else if (a.red == 2) {  // g = b*nI + m
+        b = g / nI;
+        m = g - b * nI;
+        l = base;
+      } else {                  // g = b*nmg + mg, m = mg*lpb + sl
+        const uint32_t nmg = (nI + lpb - 1) / lpb;
+        b = g / nmg;
+        m = (g - b * nmg) * lpb;
+        l = base;
+      }
+    } else if (a.tm > 0) {      // t = (b, mt, lt)
+      const uint32_t nlt = (nO + (uint32_t)a.tl - 1) / (uint32_t)a.tl;
+      const uint32_t nmt = (nI + (uint32_t)a.tm - 1) / (uint32_t)a.tm;
+      const uint32_t bm = t / nlt;
+      b = bm / nmt;
+      l = (t - bm * nlt) * (uint32_t)a.tl;
+      m = (bm - b * nmt) * (uint32_t)a.tm;
+      tmsh = 31u - (uint32_t)__builtin_clz((uint32_t)a.tm);
+    } else {
+      first = base;
+      const uint32_t bl = base / nI;
+      m = base - bl * nI;
+      b = bl / nO;
+      l = bl - b * nO;
+    }
   }
-  if (!valid) { b = 0; l = 0; m = 0; }
-  return valid;
-}
+
+  __device__ bool line(const LineDev& a, int lpb, int it, int sl, uint32_t& ob, uint32_t& ol, uint32_t& om) const {
+    const uint32_t nO = a.nO, nI = a.nI, idx = (uint32_t)(it * lpb + sl);
+    bool valid;
+    ob = b;
+    ol = l;
+    om = m;
+    if constexpr (RED) {
+      if (a.red == 1) {
+        om = m + idx;
+        valid = om < nI;
+      } else if (a.red == 2) {
+        ol = l + idx;
+        valid = ol < nO;
+      } else {
+        ol = l + (uint32_t)it;
+        om = m + (uint32_t)sl;
+        valid = ol < nO && om < nI;
+      }
+    } else if (a.tm > 0) {
+      const uint32_t il = idx >> tmsh;
+      ol = l + il;
+      om = m + (idx - (il << tmsh));
+      valid = idx < (uint32_t)a.tile && ol < nO && om < nI && b < (uint32_t)a.nb;
+    } else {
+      valid = first + idx < (uint32_t)a.nb * nO * nI;
+      om = m + idx;
+      if (om >= nI) {
+        const uint32_t c = om / nI;
+        om -= c * nI;
+        ol = l + c;
+        if (ol >= nO) {
+          const uint32_t d = ol / nO;
+          ol -= d * nO;
+          ob = b + d;
+        }
+      }
+    }
+    if (!valid) ob = ol = om = 0;
+    return valid;
+  }
+};
 
 // Padded position of element e of a wave's staging area: one pad slot per 8
 // elements, so that lanes reading rows lane*c + j (c = 8) hit distinct banks.
@@ -454,6 +496,8 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     t = blk;
   }
 
+  const BlockLines<RED> lines(a, g, t, LPB);
+
   double2 acc0[C], acc1[C];
   double2 accx0 = make_double2(0, 0), accx1 = accx0;  // the extra row (XR, last lane)
   if constexpr (RED) {
@@ -468,7 +512,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
   T pre[PREF ? NJ : 1];
   auto fetch = [&](int itn) {
     uint32_t sb, sl, sm;
-    const bool sv = decode_line(a, g, t, LPB, itn, wslot0, sb, sl, sm);
+    const bool sv = lines.line(a, LPB, itn, wslot0, sb, sl, sm);
     const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) {
@@ -497,7 +541,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     bool evalid = false;
     double2 esig = make_double2(0, 0), eip = make_double2(0, 0), ew0 = eip, ew1 = eip;
     if constexpr (EARLY || EARLY_SP) {
-      evalid = decode_line(a, g, t, LPB, it, slot, eb, el, em);
+      evalid = lines.line(a, LPB, it, slot, eb, el, em);
       esig = line_sigma(a, el, em);
       if (q > 0) eip = a.piv[(int64_t)(el * a.nI + em) * P + q];
     }
@@ -510,7 +554,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
 #pragma unroll 4
     for (int si = 0; si < SPW; ++si) {
       uint32_t sb, sl, sm;
-      const bool sv = decode_line(a, g, t, LPB, it, wslot0 + si, sb, sl, sm);
+      const bool sv = lines.line(a, LPB, it, wslot0 + si, sb, sl, sm);
       const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
       double2 al0 = make_double2(0, 0), al1 = al0, be0 = al0, be1 = al0;
       if (RANK2 && a.PO) { al0 = a.alpha0[sl]; al1 = a.alpha1[sl]; }
@@ -648,7 +692,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     if constexpr (EARLY || EARLY_SP) {
       b = eb; l = el; m = em; valid = evalid;
     } else {
-      valid = decode_line(a, g, t, LPB, it, slot, b, l, m);
+      valid = lines.line(a, LPB, it, slot, b, l, m);
     }
     const double2 sig = (EARLY || EARLY_SP) ? esig : line_sigma(a, l, m);
     RowCoef rc = coef_of_sigma(a, sig);
@@ -765,7 +809,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
 #pragma unroll 4
       for (int si = 0; si < SPW; ++si) {
         uint32_t sb, sl, sm;
-        const bool sv = decode_line(a, g, t, LPB, it, wslot0 + si, sb, sl, sm);
+        const bool sv = lines.line(a, LPB, it, wslot0 + si, sb, sl, sm);
         const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
