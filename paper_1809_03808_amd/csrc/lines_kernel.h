@@ -28,8 +28,8 @@
 // (factor_kernel; the paper likewise factors the line matrices at
 // initialisation) and stored as one reciprocal pivot per lane chunk; a solve
 // regenerates the c pivots of its chunk from it (c divisions instead of c
-// table reads) and runs the two affine scans, with wave shuffles inside a
-// wave and one LDS exchange between the waves of a line.
+// table reads) and runs the two affine scans, with moves between the registers
+// of a wave and one LDS exchange between the waves of a line.
 // Arithmetic is FP64 whatever the storage precision.
 //
 // Right-hand sides may be generated from boundary planes (the rank-2 terms of
@@ -144,10 +144,13 @@ __device__ inline Aff dpp_aff(const Aff& v) {  // identity where nothing arrives
   }
   return o;
 }
-// DPP controls (GFX9 encoding): row_shr:n = 0x110 + n, row_bcast:15 = 0x142,
-// row_bcast:31 = 0x143, wave_shr:1 = 0x138.
+// DPP controls (GFX9 encoding): row_shl:n = 0x100 + n, row_shr:n = 0x110 + n,
+// wave_shl:1 = 0x130, wave_shr:1 = 0x138, row_bcast:15 = 0x142, row_bcast:31 =
+// 0x143, row_newbcast:0 = 0x150.
+constexpr int kRowShl1 = 0x101, kRowShl2 = 0x102, kRowShl4 = 0x104, kRowShl8 = 0x108;
 constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
-constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143, kWaveShr1 = 0x138;
+constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143, kRowFirst = 0x150;
+constexpr int kWaveShl1 = 0x130, kWaveShr1 = 0x138;
 
 // Inclusive prefix composition within groups of W lanes (W = 16, 32 or 64;
 // later lanes applied after earlier ones): four in-row steps, then the row
@@ -163,34 +166,73 @@ __device__ inline Aff dpp_inclusive(Aff v) {
   return v;
 }
 
-// Lane r of each group of W lanes takes the value of lane W - 1 - r.
+// The value of the first lane of the following row (rows 0 and 2; rows 1 and 3
+// get their own first lane's).
+__device__ inline double next_row_first(double v) {
+  const unsigned long long s = __builtin_bit_cast(unsigned long long, v);
+  unsigned w[2] = {(unsigned)s, (unsigned)(s >> 32)};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const unsigned f = (unsigned)__builtin_amdgcn_mov_dpp((int)w[i], kRowFirst, 0xF, 0xF, true);
+    // swaps the odd rows of the first operand with the even rows of the second
+    w[i] = __builtin_amdgcn_permlane16_swap(f, f, false, false)[1];
+  }
+  return __builtin_bit_cast(double, ((unsigned long long)w[1] << 32) | w[0]);
+}
+__device__ inline double lane_value(double v, int l) {  // wave-uniform
+  const unsigned long long s = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)s, l);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(s >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Inclusive suffix composition (earlier lanes applied after later ones): the
+// row shifts run the other way; the total of a row is in its first lane, which
+// no row broadcast carries backwards, so rows 0 and 2 take that of rows 1 and 3
+// through a swap of rows and the lower half of the wave that of the upper half
+// through scalar registers.
 template <int W>
-__device__ inline Aff reverse_aff(const Aff& v) {
+__device__ inline Aff dpp_inclusive_rev(Aff v) {
+  v = aff_then(v, dpp_aff<kRowShl1>(v));
+  v = aff_then(v, dpp_aff<kRowShl2>(v));
+  v = aff_then(v, dpp_aff<kRowShl4>(v));
+  v = aff_then(v, dpp_aff<kRowShl8>(v));
   const int lane = threadIdx.x & 63;
-  const int src = (lane & ~(W - 1)) + (W - 1 - (lane & (W - 1)));
-  Aff o;
-  o.f = make_double2(__shfl(v.f.x, src), __shfl(v.f.y, src));
-  o.g = make_double2(__shfl(v.g.x, src), __shfl(v.g.y, src));
-  return o;
+  if constexpr (W >= 32) {
+    Aff o;
+    o.f = make_double2(next_row_first(v.f.x), next_row_first(v.f.y));
+    o.g = make_double2(next_row_first(v.g.x), next_row_first(v.g.y));
+    if (!(lane & 16)) v = aff_then(v, o);
+  }
+  if constexpr (W >= 64) {
+    Aff o;
+    o.f = make_double2(lane_value(v.f.x, 32), lane_value(v.f.y, 32));
+    o.g = make_double2(lane_value(v.g.x, 32), lane_value(v.g.y, 32));
+    if (!(lane & 32)) v = aff_then(v, o);
+  }
+  return v;
 }
 
 // Exclusive scans of affine maps over the P lanes of a line (lanes
 // [slot*P, slot*P + P) of the block).  Forward: lane q receives
-// A_{q-1} o ... o A_0; backward: lane q receives A_{q+1} o ... o A_{P-1}
-// (the forward scan in reversed lane order).  Whole waves (P >= 64) use DPP
-// moves; lines of fewer lanes use shuffles.  For P > 64 the
-// waves of a line exchange their totals through LDS (`wbuf`, NT/64 entries;
-// forward and backward scans use different buffers, so one barrier per scan
-// suffices: the next write to a buffer follows the other scan's barrier).
-// Every thread of the block must call these.
+// A_{q-1} o ... o A_0; backward: lane q receives A_{q+1} o ... o A_{P-1}.
+// Lines of 16 lanes and more scan with moves between registers, shorter ones
+// with shuffles.  (A shuffle is an LDS instruction: with shuffles at 16 and 32
+// lanes, and the backward scan of 64 lanes made a prefix scan by two reversals
+// through them, they were 96 of the 166 LDS instructions of a storing wave at
+// 256^3 FP64, and each scan six dependent LDS round trips.)
+// For P > 64 the waves of a line exchange their totals through LDS (`wbuf`,
+// NT/64 entries; forward and backward scans use different buffers, so one
+// barrier per scan suffices: the next write to a buffer follows the other
+// scan's barrier).  Every thread of the block must call these.
 template <int P>
-__device__ inline Aff wave_scan_excl(Aff v, int q, Aff& incl) {
+__device__ inline Aff scan_fwd(Aff v, int q, Aff* wbuf) {
   constexpr int W = P < 64 ? P : 64;
   Aff ex;
-  if constexpr (W == 64) {
-    v = dpp_inclusive<64>(v);
-    incl = v;
-    ex = dpp_aff<kWaveShr1>(v);
+  if constexpr (W >= 16) {
+    v = dpp_inclusive<W>(v);
+    ex = dpp_aff<W == 16 ? kRowShr1 : kWaveShr1>(v);
+    if (W == 32 && q == 0) ex = aff_ident();  // else the other line's last lane
   } else {
     const int lq = q & (W - 1);
 #pragma unroll
@@ -198,21 +240,13 @@ __device__ inline Aff wave_scan_excl(Aff v, int q, Aff& incl) {
       const Aff o = shfl_up_aff(v, d, W);
       if (lq >= d) v = aff_then(v, o);
     }
-    incl = v;
     ex = shfl_up_aff(v, 1, W);
     if (lq == 0) ex = aff_ident();
   }
-  return ex;
-}
-
-template <int P>
-__device__ inline Aff scan_fwd(Aff v, int q, Aff* wbuf) {
-  Aff incl;
-  Aff ex = wave_scan_excl<P>(v, q, incl);
   if constexpr (P > 64) {
     const int wv = threadIdx.x >> 6;          // wave in block
     const int w0 = wv - (q >> 6);             // first wave of this line
-    if ((q & 63) == 63) wbuf[wv] = incl;      // inclusive wave total
+    if ((q & 63) == 63) wbuf[wv] = v;         // inclusive wave total
     __syncthreads();
     Aff pre = aff_ident();
     for (int w = w0; w < wv; ++w) pre = aff_then(wbuf[w], pre);
@@ -224,12 +258,11 @@ __device__ inline Aff scan_fwd(Aff v, int q, Aff* wbuf) {
 template <int P>
 __device__ inline Aff scan_bwd(Aff v, int q, Aff* wbuf) {
   constexpr int W = P < 64 ? P : 64;
-  Aff ex, incl;
-  if constexpr (W == 64) {
-    // reversed lane order turns the suffix scan into a prefix scan of the
-    // same operator over the physical lane positions; in reversed order the
-    // last lane holds the composition of the whole wave
-    ex = reverse_aff<64>(wave_scan_excl<P>(reverse_aff<64>(v), q, incl));
+  Aff ex;
+  if constexpr (W >= 16) {
+    v = dpp_inclusive_rev<W>(v);
+    ex = dpp_aff<W == 16 ? kRowShl1 : kWaveShl1>(v);
+    if (W == 32 && q == P - 1) ex = aff_ident();
   } else {
     const int lq = q & (W - 1);
 #pragma unroll
@@ -243,7 +276,7 @@ __device__ inline Aff scan_bwd(Aff v, int q, Aff* wbuf) {
   if constexpr (P > 64) {
     const int wv = threadIdx.x >> 6;
     const int wl = wv - (q >> 6) + P / 64 - 1;       // last wave of this line
-    if ((threadIdx.x & 63) == 63) wbuf[wv] = incl;   // inclusive suffix total of the wave
+    if ((threadIdx.x & 63) == 0) wbuf[wv] = v;       // inclusive suffix total of the wave
     __syncthreads();
     Aff suf = aff_ident();
     for (int w = wl; w > wv; --w) suf = aff_then(wbuf[w], suf);
@@ -438,10 +471,8 @@ __device__ inline int stage_pos(int e) { return e + (e >> 3); }
 // (its pivot and value follow from the chunk's last ones), takes y_{nL-1},
 // and folds it into its backward map, which becomes the constant map to the
 // value entering its chunk from above.
-// Storing launches of exact 512-lane lines (4096-row lines) are held to 128
-// registers, so that two blocks of eight waves share a compute unit (the
-// complex64 kernel needs 131 otherwise and then spills 2; 4096^2 mixed
-// solve: line launches 0.365 -> 0.344 ms).
+// Storing launches are held to 128 registers where LDS admits four waves per
+// SIMD and the kernel comes close: exact lines of 16 to 64 and of 512 lanes.
 //
 // SPEC: sigma is real (the periodic branch of every periodised axis), so the
 // off-diagonal entry and its square are (a complex product with them takes two
@@ -450,7 +481,7 @@ __device__ inline int stage_pos(int e) { return e + (e >> 3); }
 // are the two reductions of a 3D solve in the eigenbasis, Step 1 in 2D and the
 // storing launches of the fast method.
 template <typename T, int NT, int P, int C, bool RED, bool XR, bool BAL, bool SPEC>
-__global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_kernel(LineDev a) {
+__global__ __launch_bounds__(NT, !RED && !XR && (NT == 512 || (!BAL && P >= 16 && P <= 64)) ? 4 : 1) void lines_kernel(LineDev a) {
   constexpr bool RANK2 = !(RED && SPEC);
   constexpr int NW = NT / 64;
   constexpr int PW = P < 64 ? P : 64;     // lanes of one line inside a wave
@@ -463,7 +494,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
 
   const int nL = BAL ? a.nL : P * C + (XR ? 1 : 0);
   const int nr = BAL ? a.r : P;           // lanes that own C rows
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // a line spans whole waves when P >= 64: its index is then wave-uniform
   const int slot = P >= 64 ? __builtin_amdgcn_readfirstlane(tid / P) : tid / P;
   const int q = tid - slot * P;
@@ -505,196 +536,141 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     for (int j = 0; j < C; ++j) acc0[j] = acc1[j] = make_double2(0, 0);
   }
 
-  // Reducing launches with one line per block (P >= 256) prefetch the
-  // next line's input rows into registers while the current line is solved,
-  // so the load latency overlaps the sweeps.
-  constexpr bool PREF = P >= 256 && RED && !XR;
-  T pre[PREF ? NJ : 1];
+  // Reducing launches without rank-2 rows (SPEC) load the next lines' rows,
+  // sigma, entering pivots and weights into registers while the current lines
+  // are solved: two waves per SIMD (the accumulators' registers) hide little of
+  // a load's latency (against loads at the top of the iteration: 256^3 FP64
+  // reductions 115 -> 73 us, 129^3 x 2 mixed 55 -> 37, 512^3 x 4 mixed 2.7 ->
+  // 1.75 ms, 4096^2 FP64 132 -> 97 us).  FP64 chunks of 8 rows of uneven lines
+  // and those with the extra row lack the registers; lines of fewer than 16
+  // lanes would hold the rows of 8 lines and more.
+  constexpr bool PREF = RED && SPEC && P >= 16 && (sizeof(T) == sizeof(float2) || !(XR || (BAL && C == 8)));
+  T pre[PREF ? SPW * NJ : 1];
+  double2 nsig = make_double2(0, 0), nip = nsig, nw1 = nsig;
+  bool nvalid = false;
+  // element of row r of the wave's part of a line; masked lanes read its first
+  auto row_of = [&](int r) { return wx0 + (r < seg ? r : 0); };
   auto fetch = [&](int itn) {
-    uint32_t sb, sl, sm;
-    const bool sv = lines.line(a, LPB, itn, wslot0, sb, sl, sm);
-    const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
 #pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-      const int r = jj * 64 + lane, x = wx0 + r;
-      T v;
-      v.x = 0;
-      v.y = 0;
-      if (r < seg && sv) v = reinterpret_cast<const T*>(a.in)[soff + x];
-      pre[jj] = v;
-    }
-  };
-  if constexpr (PREF) {
-    if (a.in && a.iters > 0) fetch(0);
-  }
-
-  // Reducing kernels of exact lines at P <= 64 load each line's sigma,
-  // entering pivot and reduction weights at the top of the iteration, so
-  // those loads are in flight while the right-hand side is staged instead of
-  // each being waited for where it is used (-3% per step at 256^3 and
-  // 512^3 x 16); at P = 512 the registers allow sigma and the pivot
-  // (-2% per line launch at 4096^2).  The other kernels lack the registers.
-  constexpr bool EARLY = RED && !XR && P <= 64;
-  constexpr bool EARLY_SP = RED && !XR && P == 512;
-  for (int it = 0; it < a.iters; ++it) {
-    uint32_t eb = 0, el = 0, em = 0;
-    bool evalid = false;
-    double2 esig = make_double2(0, 0), eip = make_double2(0, 0), ew0 = eip, ew1 = eip;
-    if constexpr (EARLY || EARLY_SP) {
-      evalid = lines.line(a, LPB, it, slot, eb, el, em);
-      esig = line_sigma(a, el, em);
-      if (q > 0) eip = a.piv[(int64_t)(el * a.nI + em) * P + q];
-    }
-    if constexpr (EARLY) {
-      const uint32_t wi = (a.red == 1) ? em : el;
-      if (!SPEC) ew0 = a.rho0[wi];
-      ew1 = a.rho1[wi];
-    }
-    // ---- right-hand side, staged through LDS -------------------------------
-#pragma unroll 4
     for (int si = 0; si < SPW; ++si) {
       uint32_t sb, sl, sm;
-      const bool sv = lines.line(a, LPB, it, wslot0 + si, sb, sl, sm);
-      const int64_t soff = ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
-      double2 al0 = make_double2(0, 0), al1 = al0, be0 = al0, be1 = al0;
-      if (RANK2 && a.PO) { al0 = a.alpha0[sl]; al1 = a.alpha1[sl]; }
-      if (RANK2 && a.PI) { be0 = a.beta0[sm]; be1 = a.beta1[sm]; }
-      const T* po = RANK2 && a.PO ? reinterpret_cast<const T*>(a.PO) + (int64_t)(sb * 2) * a.nI * nL + (int64_t)sm * nL : nullptr;
-      const T* pi = RANK2 && a.PI ? reinterpret_cast<const T*>(a.PI) + (int64_t)((sb * a.nO + sl) * 2) * nL : nullptr;
-      // one source at a time (each lane revisits only its own staging slots),
-      // so that at most NJ loads are in flight per lane
-      if (a.in && PREF) {
+      lines.line(a, LPB, itn, wslot0 + si, sb, sl, sm);
+      const T* in = reinterpret_cast<const T*>(a.in) + ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
+#pragma unroll
+      for (int jj = 0; jj < NJ; ++jj) pre[si * NJ + jj] = in[row_of(jj * 64 + lane)];
+    }
+    uint32_t sb, sl, sm;
+    nvalid = lines.line(a, LPB, itn, slot, sb, sl, sm);
+    nsig = line_sigma(a, sl, sm);
+    nip = q > 0 ? a.piv[(int64_t)(sl * a.nI + sm) * P + q] : make_double2(0, 0);
+    nw1 = a.rho1[(a.red == 1) ? sm : sl];
+  };
+  if constexpr (PREF) {
+    if (a.iters > 0) fetch(0);
+  }
+
+  for (int it = 0; it < a.iters; ++it) {
+    const double2 psig = nsig, pip = nip, pw1 = nw1;
+    const bool pvalid = nvalid;
+    // ---- right-hand side, staged through LDS -------------------------------
+    // A line past the end of the tile is read as line 0 and its results are
+    // dropped.
+    if constexpr (PREF) {
+#pragma unroll
+      for (int si = 0; si < SPW; ++si)
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
           const int r = jj * 64 + lane;
-          if (r < seg) S[stage_pos(si * seg + r)] = to_d2(pre[jj]);
+          if (r < seg) S[stage_pos(si * seg + r)] = to_d2(pre[si * NJ + jj]);
         }
-        if (it + 1 < a.iters) fetch(it + 1);
-      } else if (a.in) {
-        double2 d[NJ];
-        if constexpr (sizeof(T) == sizeof(float2) && !XR) {
-          // complex64 rows: loaded unconditionally (masked lanes read element
-          // 0 of the input, in bounds, and discard it) and converted after
-          // all loads are issued.  Loads under a per-row condition, each
-          // converted inside its branch, are waited for one by one
-          // (512^3 x 16 mixed step 339 -> 311 ms with this form).
-          T raw[NJ];
-#pragma unroll
-          for (int jj = 0; jj < NJ; ++jj) {
-            const int r = jj * 64 + lane, x = wx0 + r;
-            const bool ok = r < seg && sv;
-            raw[jj] = reinterpret_cast<const T*>(a.in)[ok ? soff + x : 0];
-          }
-#pragma unroll
-          for (int jj = 0; jj < NJ; ++jj) {
-            const int r = jj * 64 + lane, x = wx0 + r;
-            d[jj] = (r < seg && sv) ? to_d2(raw[jj]) : make_double2(0, 0);
-          }
-        } else {
-#pragma unroll
-          for (int jj = 0; jj < NJ; ++jj) {
-            const int r = jj * 64 + lane, x = wx0 + r;
-            d[jj] = (r < seg && sv) ? to_d2(reinterpret_cast<const T*>(a.in)[soff + x])
-                                               : make_double2(0, 0);
-          }
-        }
-#pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-          const int r = jj * 64 + lane;
-          if (r < seg) S[stage_pos(si * seg + r)] = d[jj];
-        }
-      } else {
-#pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-          const int r = jj * 64 + lane;
-          if (r < seg) S[stage_pos(si * seg + r)] = make_double2(0, 0);
-        }
-      }
-      // Rank-2 terms.  Kernels of exact lines load the rows of a source in
-      // batches of NBAT chunk rows before combining any of them into the
-      // staged values, so the loads of a batch are in flight together; loads
-      // interleaved with the LDS updates may be issued one by one, each
-      // waited for (measured at 512^3 x 16: 20-25 ms against 10-12 ms per
-      // reducing launch).  Batches cost registers: reducing kernels take
-      // all rows with several lines per block and 2 at P = 512 (at the
-      // register limit; -2% per launch at 4096^2); storing kernels at
-      // P = 16 to 64 take 4 (same occupancy; -11% per storing launch at
-      // 512^3 x 16), and with complex64 storage at P = 512 2, each batch
-      // scheduled on its own (same occupancy; -4% per line launch at 4096^2).
-      // The other kernels update row by row, which keeps their register
-      // count and occupancy (a batch would cost the other storing kernels,
-      // and the reducing ones at P = 256, an occupancy level).
-      constexpr bool SEP = !RED && P == 512 && sizeof(T) == sizeof(float2);
-      constexpr int NB0 = XR    ? 0
-                          : RED ? (P <= 128 ? NJ : (P == 512 ? 2 : 0))
-                                : ((P >= 16 && P <= 64) ? 4 : (SEP ? 2 : 0));
+      if (it + 1 < a.iters) fetch(it + 1);
+    } else {
+      // The input row and the four rank-2 rows of a batch of chunk rows (of SB
+      // lines where a line has few) are loaded before any is used, combined in
+      // registers and staged once.  Staged values updated source by source cost
+      // five LDS accesses a row instead of one and a wait per source (storing
+      // launches: 129^3 x 2 mixed 64 -> 41 us, 512^3 x 4 mixed 3.5 -> 3.06 ms,
+      // 2049^2 FP64 51 -> 39 us, 4096^2 FP64 151 -> 139 us; batches of 8 rows
+      // the same within 1%, with more registers).
+      constexpr int NB0 = RED || P <= 64 ? 4 : 2;
       constexpr int NBAT = NB0 < NJ ? NB0 : NJ;
-      if constexpr (!RANK2) {
-      } else if constexpr (NBAT > 0) {
+      constexpr int NU0 = !RED && sizeof(T) == sizeof(float2) ? 4 : 2;  // (registers)
+      constexpr int SB = NU0 / NJ < 1 ? 1 : (NU0 / NJ < SPW ? NU0 / NJ : SPW);
+      auto rhs = [&](auto has_in, auto has_po, auto has_pi) {
+        constexpr bool HI = decltype(has_in)::value, HO = decltype(has_po)::value, HP = decltype(has_pi)::value;
+#pragma unroll 1
+        for (int si = 0; si < SPW; si += SB) {
+          const T *in[SB], *po[SB], *pi[SB];
+          double2 al0[SB], al1[SB], be0[SB], be1[SB];
 #pragma unroll
-        for (int src = 0; src < 2; ++src) {
-          const T* rows = src == 0 ? po : pi;
-          if (!rows) continue;
-          const int64_t stride = src == 0 ? (int64_t)a.nI * nL : (int64_t)nL;
-          const double2 w0 = src == 0 ? al0 : be0, w1 = src == 0 ? al1 : be1;
+          for (int k = 0; k < SB; ++k) {
+            uint32_t sb, sl, sm;
+            lines.line(a, LPB, it, wslot0 + si + k, sb, sl, sm);
+            in[k] = reinterpret_cast<const T*>(a.in) + ((int64_t)(sb * a.nO + sl) * a.nI + sm) * nL;
+            po[k] = reinterpret_cast<const T*>(a.PO) + (int64_t)(sb * 2) * a.nI * nL + (int64_t)sm * nL;
+            pi[k] = reinterpret_cast<const T*>(a.PI) + (int64_t)((sb * a.nO + sl) * 2) * nL;
+            if constexpr (HO) { al0[k] = a.alpha0[sl]; al1[k] = a.alpha1[sl]; }
+            if constexpr (HP) { be0[k] = a.beta0[sm]; be1[k] = a.beta1[sm]; }
+          }
 #pragma unroll
           for (int j0 = 0; j0 < NJ; j0 += NBAT) {
-            double2 p0[NBAT], p1[NBAT];
+            constexpr int NU = SB * NBAT;
+            T v[NU], p0[NU], p1[NU], p2[NU], p3[NU];
 #pragma unroll
-            for (int u = 0; u < NBAT; ++u) {
-              const int r = (j0 + u) * 64 + lane, x = wx0 + r;
-              const bool ok = j0 + u < NJ && r < seg && sv;
-              p0[u] = ok ? to_d2(rows[x]) : make_double2(0, 0);
-              p1[u] = ok ? to_d2(rows[stride + x]) : make_double2(0, 0);
+            for (int u = 0; u < NU; ++u) {
+              const int k = u / NBAT, j = j0 + u % NBAT;
+              if (j >= NJ) continue;
+              const int x = row_of(j * 64 + lane);
+              if constexpr (HI) v[u] = in[k][x];
+              if constexpr (HO) { p0[u] = po[k][x]; p1[u] = po[k][(int64_t)a.nI * nL + x]; }
+              if constexpr (HP) { p2[u] = pi[k][x]; p3[u] = pi[k][nL + x]; }
             }
 #pragma unroll
-            for (int u = 0; u < NBAT; ++u) {
-              const int r = (j0 + u) * 64 + lane, x = wx0 + r;
-              if (j0 + u < NJ && r < seg && sv) {
-                const int q = stage_pos(si * seg + r);
-                S[q] = cfma(w1, p1[u], cfma(w0, p0[u], S[q]));
-              }
+            for (int u = 0; u < NU; ++u) {
+              const int k = u / NBAT, j = j0 + u % NBAT;
+              if (j >= NJ) continue;
+              const int r = j * 64 + lane;
+              double2 d = make_double2(0, 0);
+              if constexpr (HI) d = to_d2(v[u]);
+              if constexpr (HO) d = cfma(al1[k], to_d2(p1[u]), cfma(al0[k], to_d2(p0[u]), d));
+              if constexpr (HP) d = cfma(be1[k], to_d2(p3[u]), cfma(be0[k], to_d2(p2[u]), d));
+              if (r < seg) S[stage_pos((si + k) * seg + r)] = d;
             }
-            // keep the next batch's loads after these updates (registers)
-            if constexpr (SEP) __builtin_amdgcn_sched_barrier(0);
+            // the next batch's loads stay behind this one's registers
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
+      };
+      using std::false_type;
+      using std::true_type;
+      // one branch per set of sources: loads under a condition each are
+      // converted inside it and waited for one by one (512^3 x 4 mixed 4.4 ms)
+      const bool hi = a.in, ho = RANK2 && a.PO, hp = RANK2 && a.PI;
+      if constexpr (!RANK2) {
+        rhs(true_type{}, false_type{}, false_type{});
+      } else if (hi) {
+        if (ho && hp) rhs(true_type{}, true_type{}, true_type{});
+        else if (ho) rhs(true_type{}, true_type{}, false_type{});
+        else if (hp) rhs(true_type{}, false_type{}, true_type{});
+        else rhs(true_type{}, false_type{}, false_type{});
       } else {
-        if (po) {
-#pragma unroll
-          for (int jj = 0; jj < NJ; ++jj) {
-            const int r = jj * 64 + lane, x = wx0 + r;
-            if (r < seg && sv) {
-              double2 d = S[stage_pos(si * seg + r)];
-              d = cfma(al0, to_d2(po[x]), d);
-              d = cfma(al1, to_d2(po[(int64_t)a.nI * nL + x]), d);
-              S[stage_pos(si * seg + r)] = d;
-            }
-          }
-        }
-        if (pi) {
-#pragma unroll
-          for (int jj = 0; jj < NJ; ++jj) {
-            const int r = jj * 64 + lane, x = wx0 + r;
-            if (r < seg && sv) {
-              double2 d = S[stage_pos(si * seg + r)];
-              d = cfma(be0, to_d2(pi[x]), d);
-              d = cfma(be1, to_d2(pi[nL + x]), d);
-              S[stage_pos(si * seg + r)] = d;
-            }
-          }
-        }
+        if (ho && hp) rhs(false_type{}, true_type{}, true_type{});
+        else if (ho) rhs(false_type{}, true_type{}, false_type{});
+        else if (hp) rhs(false_type{}, false_type{}, true_type{});
+        else rhs(false_type{}, false_type{}, false_type{});
       }
     }
 
     uint32_t b, l, m;
     bool valid;
-    if constexpr (EARLY || EARLY_SP) {
-      b = eb; l = el; m = em; valid = evalid;
+    if constexpr (PREF && !XR) {
+      b = l = m = 0;
+      valid = pvalid;
     } else {
       valid = lines.line(a, LPB, it, slot, b, l, m);
     }
-    const double2 sig = (EARLY || EARLY_SP) ? esig : line_sigma(a, l, m);
+    const double2 sig = PREF ? psig : line_sigma(a, l, m);
     RowCoef rc = coef_of_sigma(a, sig);
     if (SPEC) rc.dint.y = 0.0;
     const double2 moff = make_double2(-rc.off.x, -rc.off.y);  // -e
@@ -727,9 +703,12 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     // Reciprocal pivots: the chunk's entering value from the plan's factor
     // table, then the Thomas recurrence p_x = d_x - e^2 / p_{x-1}.
     // Forward substitution z_x = f_x z_{x-1} + d_x, f_x = -e / p_{x-1}: the
-    // lane composes its rows into one affine map.
-    const double2 ip_in = (EARLY || EARLY_SP) ? eip : (q > 0 ? a.piv[(int64_t)(l * a.nI + m) * P + q] : make_double2(0, 0));
-    Aff A = aff_ident();
+    // lane composes its rows into one affine map.  With m_x = -e / p_x its
+    // factor is m_in m_x0 ... m_{last-1} and that of the backward map below
+    // m_x0 ... m_last, so the product R of the common ones is formed once.
+    const double2 ip_in = PREF ? pip : (q > 0 ? a.piv[(int64_t)(l * a.nI + m) * P + q] : make_double2(0, 0));
+    Aff A;
+    double2 R = make_double2(1, 0);
     double2 ipp_last;  // 1/p of the chunk's last row
     {
       double2 ipp = ip_in;
@@ -737,8 +716,12 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
       for (int j = 0; j < C; ++j) {
         if (has_row(j)) {
           const double2 f = mul_moff(ipp);
-          A.f = cmul(f, A.f);
-          A.g = cfma(f, A.g, z[j]);
+          if (j == 0) {
+            A.g = z[0];
+          } else {
+            R = j == 1 ? f : cmul(f, R);
+            A.g = cfma(f, A.g, z[j]);
+          }
           const bool end = !XR && q == P - 1 && (j == C - 1 || (BAL && j == C - 2 && !full));
           double2 pv = (j == 0 && q == 0) ? rc.dlo : (end ? rc.dhi : rc.dint);
           pv = sub_off2(ipp, pv);  // ipp = 0 at x = 0
@@ -747,7 +730,11 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
         }
       }
       ipp_last = ipp;
+      A.f = cmul(mul_moff(ip_in), R);
     }
+    // (the parked values are read back: kept in registers across the scans,
+    // 40 more, they cost an occupancy level or the prefetch)
+    asm volatile("" ::: "memory");
     const Aff Ein = scan_fwd<P>(A, q, wbuf[0]);
 
     // ---- 2. forward values, scaled for the back substitution --------------
@@ -774,20 +761,18 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
       }
     }
 
+    asm volatile("" ::: "memory");
     // ---- 3. back substitution y_x = g_x y_{x+1} + h_x: composition, scan ---
-    Aff B = aff_ident();
+    Aff B;
+    B.f = cmul(mul_moff(ipp_last), R);
+    B.g = z[C - 1];
 #pragma unroll
-    for (int j = C - 1; j >= 0; --j) {
-      if (has_row(j)) {
-        const double2 gx = S[slot_of(j)];
-        B.f = cmul(gx, B.f);
-        B.g = cfma(gx, B.g, z[j]);
-      }
-    }
+    for (int j = C - 2; j >= 0; --j) B.g = cfma(S[slot_of(j)], B.g, z[j]);
     if (XR && last) {  // the value above the chunk is known: a constant map
       B.g = cfma(B.f, yx, B.g);
       B.f = make_double2(0, 0);
     }
+    asm volatile("" ::: "memory");
     const Aff Bin = scan_bwd<P>(B, q, wbuf[1]);
     {
       double2 ynext = (XR && last) ? yx : Bin.g;
@@ -822,7 +807,7 @@ __global__ __launch_bounds__(NT, (!RED && NT == 512 && !XR) ? 4 : 1) void lines_
     if constexpr (RED) {
       if (valid) {
         const uint32_t wi = (a.red == 1) ? m : l;
-        const double2 w0 = EARLY ? ew0 : (SPEC ? make_double2(0, 0) : a.rho0[wi]), w1 = EARLY ? ew1 : a.rho1[wi];
+        const double2 w0 = SPEC ? make_double2(0, 0) : a.rho0[wi], w1 = PREF ? pw1 : a.rho1[wi];
         if (XR && last) {
           accx0 = SPEC ? cadd(yx, accx0) : cfma(w0, yx, accx0);
           accx1 = cfma(w1, yx, accx1);

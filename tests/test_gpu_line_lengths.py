@@ -48,3 +48,19 @@ def test_2d_line_lengths(n, prec):
 def test_3d_line_lengths(grid, prec, boundary, layout, monkeypatch):
     monkeypatch.setenv("HELM_RED_L_LAYOUT", layout)
     _check(grid, prec, boundary=boundary)
+
+
+# Blocks that take several lines one after the other, the last tile ragged: the
+# reducing kernels load a line's rows while the one before is solved.
+@pytest.mark.parametrize("prec", [helm.PREC_FP64, helm.PREC_MIXED])
+@pytest.mark.parametrize("grid", [(75, 320), (83, 513), (37, 1024), (43, 2049), (27, 4096), (75, 600), (41, 1500)])
+def test_2d_several_lines_per_block(grid, prec):
+    _check(grid, prec)
+
+
+@pytest.mark.parametrize("layout", ["2", "3"])
+@pytest.mark.parametrize("grid,prec", [((67, 29, 100), helm.PREC_MIXED), ((35, 61, 128), helm.PREC_FP64),
+                                       ((33, 47, 256), helm.PREC_FP64), ((37, 31, 200), helm.PREC_MIXED)])
+def test_3d_several_lines_per_block(grid, prec, layout, monkeypatch):
+    monkeypatch.setenv("HELM_RED_L_LAYOUT", layout)
+    _check(grid, prec)
