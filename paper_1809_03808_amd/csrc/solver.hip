@@ -155,6 +155,7 @@ struct helm_plan {
                 *mG1 = nullptr, *mG2 = nullptr;
   int modal_min_nb = 0;
   int red_layout = 2;  // layout of the line reductions over the outer modes (2 or 3)
+  bool lean_parts = false;  // fewest partial sums (solves in the fixed static scratch that would not fit otherwise)
   int fft_small = 0;   // 512-point passes: 0 the 128 KB tile, 1 the 64 KB complex64 tile, 2 streaming (tuned)
   double modal_ms[4] = {-1, -1, -1, -1};  // measured: lines at 1 and 16 RHS, tables at 1 and 16 RHS
   std::string tune_path;
@@ -771,17 +772,20 @@ int run_fft(helm_plan* p, const PAxis& a, int sign, bool fp32, const void* in, i
 int red_l_mode(const helm_plan* p) { return p->red_layout; }
 
 // Lines per tile and tiles of a line launch; `layout` (2 or 3) only matters
-// for red 2.  At least 8 lines feed each partial sum of layouts 1 and 2
-// (partials stay below 1/4 of an N-sized array).  A reducing launch writes one
+// for red 2.  At least 4 lines feed each partial sum of layouts 1 and 2
+// (partials stay below 1/2 of an N-sized array).  A reducing launch writes one
 // partial of 2 nL values per block (layout 3: per slot), and R blocks stay
 // resident at once (one 512-thread or two 256-thread blocks per compute unit at
 // the register use of the reducing kernels), so its tiles are those that take
 // the fewest iterations in rounds of R blocks, a block's start and partials
 // counted as 0.7 of an iteration: 512 blocks at 256^3, and not the 516 that
 // left four blocks to a second round at 129^3 x 2 (70 us; 774 blocks of two
-// thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us).
+// thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us); 410
+// blocks of 5 lines at 2049^2 instead of 257 of 8 (40 + 47 -> 34 + 42 us, the sums
+// of the partials 2 us more).
+// `lean` keeps to the partials of one round of blocks, of at least 8 lines.
 // Other launches take up to 2048 blocks.
-void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, int* tile, int* ntiles) {
+void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, bool lean, int* tile, int* ntiles) {
   int P, c, NT;
   lines_geometry(nL, &P, &c, &NT);
   const int LPB = NT / P;
@@ -799,9 +803,10 @@ void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, int* 
   const int64_t extent = red == 1 ? nI : nO;
   const int64_t groups = (int64_t)nb * (red == 1 ? nO : (l3 ? (nI + LPB - 1) / LPB : nI));
   // lines per iteration of a block along the reduced index, and per tile
-  const int64_t step = l3 ? 1 : LPB, tmin = l3 ? 1 : std::min<int64_t>(8, extent);
+  const int64_t step = l3 ? 1 : LPB, tmin = l3 ? 1 : std::min<int64_t>(lean ? 8 : 4, extent);
+  const int64_t most = lean ? R : 8 * R;  // blocks
   double best = 1e300;
-  for (int64_t n = 1; n <= extent && (n == 1 || groups * n <= 8 * R); ++n) {
+  for (int64_t n = 1; n <= extent && (n == 1 || groups * n <= most); ++n) {
     int64_t t = std::max((extent + n - 1) / n, tmin);
     t = (t + step - 1) / step * step;
     const int64_t nt = (extent + t - 1) / t;
@@ -815,15 +820,15 @@ void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, int* 
 }
 
 void tiles_for(const helm_plan* p, int red, int nb, int nO, int nI, int nL, int* tile, int* ntiles) {
-  tiles_for_layout(red, red == 2 ? red_l_mode(p) : red, nb, nO, nI, nL, tile, ntiles);
+  tiles_for_layout(red, red == 2 ? red_l_mode(p) : red, nb, nO, nI, nL, p->lean_parts, tile, ntiles);
 }
 
 // Partial sums of a reducing launch; for red 2 the larger of the two layouts,
 // so that the buffer fits whichever layout a later solve takes.
-size_t part_elems(int red, int nb, int nO, int nI, int nL) {
+size_t part_elems(int red, int nb, int nO, int nI, int nL, bool lean) {
   int tile, nt, nt3 = 0;
-  tiles_for_layout(red, 2, nb, nO, nI, nL, &tile, &nt);
-  if (red == 2) tiles_for_layout(red, 3, nb, nO, nI, nL, &tile, &nt3);
+  tiles_for_layout(red, 2, nb, nO, nI, nL, lean, &tile, &nt);
+  if (red == 2) tiles_for_layout(red, 3, nb, nO, nI, nL, lean, &tile, &nt3);
   const int64_t groups = red == 1 ? (int64_t)nb * nO : (int64_t)nb * nI;
   return (size_t)groups * std::max(nt, nt3) * 2 * nL;
 }
@@ -1466,10 +1471,10 @@ std::array<size_t, WS_N> workspace_bytes(const helm_plan* p, int nb, bool fp32, 
   // partial sums: max over the reductions used
   size_t pe = 0;
   if (p->dim == 2) {
-    pe = part_elems(1, nb, 1, p->ax[0].n, p->nL);
+    pe = part_elems(1, nb, 1, p->ax[0].n, p->nL, p->lean_parts);
   } else {
-    pe = std::max(part_elems(1, nb, p->ax[0].n, p->ax[1].n, p->nL),
-                  part_elems(2, nb, p->ax[0].n, p->ax[1].n, p->nL));
+    pe = std::max(part_elems(1, nb, p->ax[0].n, p->ax[1].n, p->nL, p->lean_parts),
+                  part_elems(2, nb, p->ax[0].n, p->ax[1].n, p->nL, p->lean_parts));
   }
   w[WS_PART] = pe * sizeof(double2);
   const int64_t nO = p->dim == 2 ? 1 : p->ax[0].n;
@@ -1933,6 +1938,7 @@ struct StaticWorkspace {
     }
     p->prof = prof;
     p->no_alloc = false;
+    p->lean_parts = false;
   }
 };
 
@@ -1952,10 +1958,19 @@ int solve_static(helm_plan* p, const void* f, void* u, int nrhs, hipStream_t st)
   rep.rel_residual_max = -1;
   rep.rel_residual_first = -1;
   if (nrhs > HELM_STATIC_MAX_RHS) return rep.status = HELM_ENOMEM;
-  const auto w = workspace_bytes(p, nrhs, mixed, check);
+  std::array<size_t, WS_N> w{};
   size_t total = 0;
-  for (size_t b : w) total += round256(b);
-  if (total > (size_t)HELM_STATIC_SCRATCH_BYTES) return rep.status = HELM_ENOMEM;
+  for (int lean = 0; lean < 2; ++lean) {  // more partial sums are faster, but never refuse a call
+    p->lean_parts = lean != 0;
+    w = workspace_bytes(p, nrhs, mixed, check);
+    total = 0;
+    for (size_t b : w) total += round256(b);
+    if (total <= (size_t)HELM_STATIC_SCRATCH_BYTES) break;
+  }
+  if (total > (size_t)HELM_STATIC_SCRATCH_BYTES) {
+    p->lean_parts = false;
+    return rep.status = HELM_ENOMEM;
+  }
   StaticWorkspace ws(p, w);
   const double2* F = reinterpret_cast<const double2*>(f);
   double2* U = reinterpret_cast<double2*>(u);
@@ -2111,7 +2126,7 @@ int measure_boundary(helm_plan* p, int nb, double* t_lines, double* t_modal) {
   const size_t e1 = (size_t)nb * n1 * 2 * nL, e2 = (size_t)nb * n2 * 2 * nL;
   DevMem pi, part, w;
   HCHK(pi.ensure(e1 * sizeof(double2)));
-  HCHK(part.ensure(part_elems(1, nb, n1, n2, nL) * sizeof(double2)));
+  HCHK(part.ensure(part_elems(1, nb, n1, n2, nL, p->lean_parts) * sizeof(double2)));
   HCHK(w.ensure((3 * e1 + 4 * e2) * sizeof(double2)));
   HCHK(hipMemset(pi.p, 0x3f, pi.bytes));  // finite values of order 1e-3
   HCHK(hipMemset(w.p, 0x3f, w.bytes));
@@ -2201,7 +2216,7 @@ int tune_layout(helm_plan* p) {
   DevMem in, pi, part;
   HCHK(in.ensure((size_t)n1 * n2 * nL * esz));
   HCHK(pi.ensure((size_t)n1 * 2 * nL * sizeof(double2)));
-  HCHK(part.ensure(part_elems(2, 1, n1, n2, nL) * sizeof(double2)));
+  HCHK(part.ensure(part_elems(2, 1, n1, n2, nL, p->lean_parts) * sizeof(double2)));
   HCHK(hipMemset(in.p, 0x3f, in.bytes));  // finite values of order 1e-3 (1 in complex64)
   HCHK(hipMemset(pi.p, 0x3f, pi.bytes));
   LineArgs la;
@@ -2233,7 +2248,7 @@ int tune_layout(helm_plan* p) {
   double best[2] = {1e30, 1e30};
   for (int v = 0; v < 2 && !rc; ++v) {
     la.red = 2 + v;
-    tiles_for_layout(2, la.red, 1, n1, n2, nL, &la.tile, &la.ntiles);
+    tiles_for_layout(2, la.red, 1, n1, n2, nL, p->lean_parts, &la.tile, &la.ntiles);
     for (int rep = 0; rep < 4 && !rc; ++rep) {
       float ms = 0;
       if (hipEventRecord(e0, nullptr) != hipSuccess || launch_lines(la, nullptr) != hipSuccess ||
