@@ -165,6 +165,7 @@ struct PassDev {
   int tw4_mode, conj_out;
   int64_t I, od, in_so, in_sj, out_so1, out_so2, out_sk, tw4_S;
   int64_t ntile;  // tiles along I
+  int64_t i_first = 0;  // first column of a convolution pass
   double scale_c;
   const void* tw;
   const void* tw4;
@@ -218,11 +219,18 @@ template <typename C> constexpr int narrow_w(int L) {
 // complex128 columns, a 64 KB tile (WO = -2, 512 threads, two blocks per compute
 // unit) half of them; the plan's tuner times both against two passes.
 constexpr int kHalf = -2;
+// The narrow tile of 512 threads for the last columns of a convolution over 2048
+// or 4096 points (launch_conv_L), which run alone: one column of 4096
+// complex128 points in 19 us, with 256 threads 21.
+constexpr int kTail = -3;
+template <typename C> constexpr int tail_w(int L) { return std::max(512 * 8 / L, 16 / (int)sizeof(C)); }
 template <int L, typename C, int WO> constexpr int tile_w_of() {
-  return WO == kHalf ? tile_w<C>(L) / 2 : (WO < 0 ? narrow_w<C>(L) : (WO ? WO : tile_w<C>(L)));
+  return WO == kHalf   ? tile_w<C>(L) / 2
+         : WO == kTail ? tail_w<C>(L)
+                       : (WO < 0 ? narrow_w<C>(L) : (WO ? WO : tile_w<C>(L)));
 }
 template <int L, int WO> constexpr int threads_for() {
-  return WO == kHalf ? 512 : (WO < 0 ? narrow_threads(L) : threads_of(L));
+  return WO == kHalf || WO == kTail ? 512 : (WO < 0 ? narrow_threads(L) : threads_of(L));
 }
 template <int L, typename C, int WO> constexpr int min_waves_of() { return WO > 0 ? 8 : (WO == kHalf ? 4 : 1); }
 
@@ -570,7 +578,7 @@ __global__ __launch_bounds__((threads_for<L, WO>())) void conv_pass_kernel(PassD
   PassDev p = p0;
   const uint32_t blk = (uint32_t)tile_of_block<W, C>(blockIdx.x, gridDim.x), nt = (uint32_t)p.ntile;
   const uint32_t o = blk / nt;
-  const int64_t i0 = (int64_t)(blk - o * nt) * W;
+  const int64_t i0 = p.i_first + (int64_t)(blk - o * nt) * W;
   int64_t oq = o, orr = 0;
   if constexpr (ONE) {
     p.od = 1;
@@ -609,14 +617,14 @@ template <int L, typename C> bool narrow_launch(const PassDev& p, int64_t O) {
   return WN < W && p.I > WN && O * ((p.I + W - 1) / W) < compute_units();
 }
 
-template <int L, typename C, int WO = 0>
-hipError_t launch_conv_L(const PassDev& p, int64_t O, const void* in, void* out, hipStream_t s) {
-  if constexpr (WO == 0 && L >= 64) {
-    if (narrow_launch<L, C>(p, O)) return launch_conv_L<L, C, -1>(p, O, in, out, s);
-  }
+// Columns [first, first + count) in tiles of WO.
+template <int L, typename C, int WO>
+hipError_t launch_conv_cols(const PassDev& p, int64_t O, int64_t first, int64_t count, const void* in, void* out,
+                            hipStream_t s) {
   constexpr int W = tile_w_of<L, C, WO>();
   PassDev q = p;
-  q.ntile = (p.I + W - 1) / W;
+  q.i_first = first;
+  q.ntile = (count + W - 1) / W;
   const int64_t blocks = O * q.ntile;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -631,6 +639,28 @@ hipError_t launch_conv_L(const PassDev& p, int64_t O, const void* in, void* out,
     }
   }
   return hipGetLastError();
+}
+
+// The 128 KB tiles run one per compute unit, in rounds.  Where the columns past
+// the last full tile would open a round of their own (2^k + 1 columns: the
+// paper's grids), they go to narrow tiles in a launch after the full ones, which
+// take 11 to 19 us against a round of 20 to 30 (513^2 x 4 FP64 40 -> 35 us,
+// 1025^2 x 4 mixed 110 -> 90, 257 x 2049 x 8 mixed 72 -> 57, 2049^2 FP64 127 -> 124).
+template <int L, typename C> hipError_t launch_conv_L(const PassDev& p, int64_t O, const void* in, void* out, hipStream_t s) {
+  if constexpr (L >= 64) {
+    if (narrow_launch<L, C>(p, O)) return launch_conv_cols<L, C, -1>(p, O, 0, p.I, in, out, s);
+  }
+  if constexpr (L >= 512) {
+    constexpr int WT = L == 2048 || L == 4096 ? kTail : -1;
+    constexpr int W = tile_w<C>(L), WN = tile_w_of<L, C, WT>();
+    const int64_t full = O * (p.I / W), rest = p.I % W, cu = compute_units();
+    if (WN < W && rest > 0 && rest <= WN && full >= cu && (full + cu - 1) / cu < (full + O + cu - 1) / cu) {
+      const hipError_t e = launch_conv_cols<L, C, 0>(p, O, 0, p.I - rest, in, out, s);
+      if (e != hipSuccess) return e;
+      return launch_conv_cols<L, C, WT>(p, O, p.I - rest, rest, in, out, s);
+    }
+  }
+  return launch_conv_cols<L, C, 0>(p, O, 0, p.I, in, out, s);
 }
 
 template <typename C>
