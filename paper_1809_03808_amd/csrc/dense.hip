@@ -22,6 +22,9 @@ namespace {
 template <typename C> struct RealT;
 template <> struct RealT<double2> { using T = double; };
 template <> struct RealT<float2> { using T = float; };
+template <typename R> struct CplxT;
+template <> struct CplxT<double> { using T = double2; };
+template <> struct CplxT<float> { using T = float2; };
 
 template <typename R, typename TIN, typename TOUT, int T>
 __global__ __launch_bounds__(256) void dense_kernel(DenseArgs a) {
@@ -40,25 +43,14 @@ __global__ __launch_bounds__(256) void dense_kernel(DenseArgs a) {
   const int m0 = mi * G::B;
   const int64_t x0 = xi * G::B;
   const TIN* in = reinterpret_cast<const TIN*>(a.in) + beta * (int64_t)n * S;
-  const R* Q = reinterpret_cast<const R*>(a.Q);  // interleaved complex [n][n]
+  const typename CplxT<R>::T* Q = reinterpret_cast<const typename CplxT<R>::T*>(a.Q);  // [n][n]
   typename G::acc cr[T][T], ci[T][T];
   G::template run<false>(
       lds, n,
-      [&](int k, int mm, R& re, R& im) {  // A[m][k] = Q[k][m], rows k of Q are contiguous in m
-        const int m = m0 + mm;
-        if (m < n) {
-          re = Q[2 * ((int64_t)k * n + m)];
-          im = Q[2 * ((int64_t)k * n + m) + 1];
-        }
-      },
-      [&](int k, int xx, R& re, R& im) {  // rows k of the input block, contiguous in x
-        const int64_t x = x0 + xx;
-        if (x < S) {
-          const TIN v = in[(int64_t)k * S + x];
-          re = (R)v.x;
-          im = (R)v.y;
-        }
-      },
+      // A[m][k] = Q[k][m], rows k of Q are contiguous in m
+      [&](int k, int mm) { return Q[(int64_t)k * n + min(m0 + mm, n - 1)]; },
+      // rows k of the input block, contiguous in x
+      [&](int k, int xx) { return in[(int64_t)k * S + (x0 + xx < S ? x0 + xx : S - 1)]; },
       cr, ci);
   TOUT* out = reinterpret_cast<TOUT*>(a.out) + beta * (int64_t)n * S;
   G::each(cr, ci, [&](int mm, int xx, R re, R im) {

@@ -82,21 +82,8 @@ __global__ __launch_bounds__(256) void modal_rows_kernel(const double2* __restri
   typename G::acc cr[T][T], ci[T][T];
   G::template run<true>(
       lds, nL,
-      [&](int k, int mm, double& re, double& im) {
-        const int64_t r = r0 + mm;
-        if (r < rows) {
-          const double2 v = s.in[r * nL + k];
-          re = v.x;
-          im = v.y;
-        }
-      },
-      [&](int k, int xx, double& re, double& im) {
-        if (x0 + xx < nL) {
-          const double2 v = Q[(int64_t)k * nL + x0 + xx];
-          re = v.x;
-          im = v.y;
-        }
-      },
+      [&](int k, int mm) { return s.in[(r0 + mm < rows ? r0 + mm : rows - 1) * nL + k]; },
+      [&](int k, int xx) { return Q[(int64_t)k * nL + min(x0 + xx, nL - 1)]; },
       cr, ci);
   G::each(cr, ci, [&](int mm, int xx, double re, double im) {
     const int64_t r = r0 + mm;
