@@ -77,11 +77,11 @@ def _source_hash(paths):
 
 _H = "paper_1809_03808_amd/csrc/helm_internal.h"
 KERNEL_SOURCES = {
-    "lines_kernel": ["paper_1809_03808_amd/csrc/lines.hip", _H],
+    "lines_kernel": ["paper_1809_03808_amd/csrc/lines_kernel.h", "paper_1809_03808_amd/csrc/lines.hip", _H],
     "fft_pass_kernel<double2>": ["paper_1809_03808_amd/csrc/fft.hip", _H],
     "fft_pass_kernel<float2>": ["paper_1809_03808_amd/csrc/fft.hip", _H],
     "residual_kernel": ["paper_1809_03808_amd/csrc/stencil.hip", _H],
-    "dense_kernel": ["paper_1809_03808_amd/csrc/dense.hip", _H],
+    "dense_kernel": ["paper_1809_03808_amd/csrc/dense.hip", "paper_1809_03808_amd/csrc/cgemm.h", _H],
 }
 
 

@@ -29,7 +29,7 @@
  *     the same sums) and keeps the faster; HELM_RED_L_LAYOUT=2 or 3 in the
  *     environment at setup fixes the choice instead (tests).  With
  *     helm_options.tune_cache set, this and the other measured choices
- *     (transform, boundary tables) are read from / appended to that file.
+ *     (transform, boundary steps) are read from / appended to that file.
  */
 #ifndef HELM_H
 #define HELM_H
@@ -272,7 +272,7 @@ int helm_residual(helm_plan* p, const void* u, const void* f, void* r,
  * the summed algorithmic bytes (the N-sized arrays each launch must read and
  * write once: 2 x element size per unknown for a transform pass, 1x, 0x or 2x
  * for the Step 1 / Step 2 / Step 3 line solves, 32 bytes for the FP64
- * residual; the table bytes for the boundary-table products).  reset != 0
+ * residual; the boundary vectors for the eigenbasis boundary steps).  reset != 0
  * clears the accumulators afterwards.
  */
 #define HELM_NKERNELS 9
