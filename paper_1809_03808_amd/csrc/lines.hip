@@ -1,5 +1,6 @@
 // Batched tridiagonal solves: geometry, factor tables and launches (the kernels
 // are in lines_kernel.h).
+#include "dd.h"
 #include "lines_kernel.h"
 
 namespace helm {
@@ -20,54 +21,30 @@ namespace {
 using namespace linek;
 
 // Factor table: for every line matrix (l, m) and lane chunk q, the reciprocal
-// pivot entering the chunk of the Thomas elimination.  Lane q
-// composes the Moebius maps of its rows and a scan over the lanes gives the
-// pivot state entering each chunk.  Runs once per plan; one block of P lanes
-// per line.  The solves regenerate the pivots inside each chunk from it.
-__global__ void factor_kernel(LineDev a, int P, double2* piv) {
-  extern __shared__ double smem_d[];
-  Mob* buf = reinterpret_cast<Mob*>(smem_d);
-  const int q = threadIdx.x;
-  const int64_t line = blockIdx.x;  // l * nI + m
-  const int64_t l = line / a.nI, m = line % a.nI;
-  const RowCoef rc = row_coef(a, l, m);
-  const int x0 = chunk_start(q, a.c, a.r), rows = q < a.r ? a.c : a.c - 1;
-  Mob G;
-  G.a = make_double2(1, 0); G.b = make_double2(0, 0);
-  G.c = make_double2(0, 0); G.d = make_double2(1, 0);
-  for (int j = 0; j < rows; ++j) {
-    const int x = x0 + j;
-    const double2 dg = diag_of(rc, x, a.nL);
-    const double2 e2 = has_e(x, a.nL) ? rc.off2 : make_double2(0, 0);
-    Mob n;
-    n.a = csub(cmul(dg, G.a), cmul(e2, G.c));
-    n.b = csub(cmul(dg, G.b), cmul(e2, G.d));
-    n.c = G.a;
-    n.d = G.b;
-    G = n;
+// pivot entering the chunk of the Thomas elimination, 1/p_x = 1 / (d_x - e^2 / p_{x-1})
+// over the rows before it.  One thread per line, once per plan, in double-double
+// arithmetic on the coefficients that the solves round: an entering pivot that
+// differs from the one that the rows before it end with changes the matrix at
+// that chunk boundary, so the rounding errors gathered over all rows must not
+// reach the table.  (Composed in FP64 as 2 x 2 Moebius maps in a scan over the
+// chunks, they were most of the residual of a plain FP64 solve: 256^3 at 10 points
+// per wavelength 7.0e-11 with line sweeps and 7.4e-11 with the boundary steps in the
+// eigenbasis, which does not share them, now 8.7e-13 and 9.7e-13; 4096^2 3.1e-9,
+// now 4.8e-11, and 5.2e-11 with the recurrence in FP64.)
+__global__ __launch_bounds__(64) void factor_kernel(LineDev a, int P, int64_t lines, double2* piv) {
+  const int64_t line = (int64_t)blockIdx.x * 64 + threadIdx.x;  // l * nI + m
+  if (line >= lines) return;
+  const RowCoef rc = coef_of_sigma(a, line_sigma(a, line / a.nI, line % a.nI));
+  double2* out = piv + line * P;
+  out[0] = make_double2(0, 0);
+  const cdd one = cdd_of(make_double2(1, 0)), e2 = cdd_of(rc.off2);
+  cdd ip = cdd_zero();
+  int x = 0;
+  for (int q = 1; q < P; ++q) {
+    for (const int end = chunk_start(q, a.c, a.r); x < end; ++x)
+      ip = cdd_div(one, cdd_sub(cdd_of(x == 0 ? rc.dlo : rc.dint), cdd_mul(e2, ip)));
+    out[q] = make_double2(ip.re.hi, ip.im.hi);
   }
-  mob_norm(G);
-  // Hillis-Steele inclusive scan (later * earlier), then shift.
-  buf[q] = G;
-  __syncthreads();
-  for (int d = 1; d < P; d <<= 1) {
-    Mob mine = buf[q];
-    Mob other = q >= d ? buf[q - d] : mine;
-    __syncthreads();
-    if (q >= d) {
-      mine = mob_mul(mine, other);
-      mob_norm(mine);
-      buf[q] = mine;
-    }
-    __syncthreads();
-  }
-  double2 ip = make_double2(0, 0);
-  if (q > 0) {
-    const Mob E = buf[q - 1];
-    // state entering the chunk: E (1, 0)^T = (E.a, E.c), 1/p = E.c / E.a
-    ip = cmul(E.c, crcp(E.a));
-  }
-  piv[line * P + q] = ip;
 }
 
 LineDev make_dev(const LineArgs& a, int P, int c) {
@@ -117,7 +94,7 @@ hipError_t launch_line_factors(const LineArgs& a, double2* piv, hipStream_t s) {
   const LineDev d = make_dev(a, P, c);
   const int64_t lines = (int64_t)a.nO * a.nI;
   if (lines <= 0) return hipSuccess;
-  hipLaunchKernelGGL(factor_kernel, dim3((unsigned)lines), dim3(P), (size_t)P * sizeof(Mob), s, d, P, piv);
+  hipLaunchKernelGGL(factor_kernel, dim3((unsigned)((lines + 63) / 64)), dim3(64), 0, s, d, P, lines, piv);
   return hipGetLastError();
 }
 

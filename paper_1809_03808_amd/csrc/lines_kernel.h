@@ -16,20 +16,18 @@
 // for some sigma; it is not used.
 //
 // Parallelism.  A line of nL rows is owned by P lanes (P a power of two, one
-// wave or a few), lane q holding the rows [q c, q c + c).  The recurrences of
+// wave or a few), lane q holding the rows [q c, q c + c).  The substitutions of
 // Thomas are associative and are evaluated by exclusive scans across the P
 // lanes:
-//   pivots   (num, den) -> (d num - e^2 den, num)       2x2 Moebius matrices
 //   forward  z_x = d_x - e_x / p_{x-1} z_{x-1}          affine maps z -> F z + G
 //   backward y_x = (z_x - e_{x+1} y_{x+1}) / p_x       affine maps, reversed
 // Each lane composes its c rows, the scan supplies the state entering the
-// chunk, and the lane then re-runs its rows sequentially.  The pivot state
-// entering each chunk depends on sigma only, so it is computed once per plan
-// (factor_kernel; the paper likewise factors the line matrices at
-// initialisation) and stored as one reciprocal pivot per lane chunk; a solve
-// regenerates the c pivots of its chunk from it (c divisions instead of c
-// table reads) and runs the two affine scans, with moves between the registers
-// of a wave and one LDS exchange between the waves of a line.
+// chunk, and the lane then re-runs its rows sequentially.  The pivots depend on
+// sigma only: the reciprocal pivot entering each chunk is computed once per plan
+// (factor_kernel, row after row; the paper likewise factors the line matrices
+// at initialisation), and a solve regenerates the c pivots of its chunk from it
+// (c divisions instead of c table reads).  Moves between lanes are register moves
+// inside a wave and one LDS exchange between the waves of a line.
 // Arithmetic is FP64 whatever the storage precision.
 //
 // Right-hand sides may be generated from boundary planes (the rank-2 terms of
@@ -44,36 +42,9 @@ namespace helm {
 
 namespace linek {
 
-struct Mob {  // 2x2 complex matrix [[a, b], [c, d]]
-  double2 a, b, c, d;
-};
 struct Aff {  // z -> f z + g
   double2 f, g;
 };
-
-__device__ inline Mob mob_mul(const Mob& L, const Mob& R) {  // L * R
-  Mob o;
-  o.a = cfma(L.a, R.a, cmul(L.b, R.c));
-  o.b = cfma(L.a, R.b, cmul(L.b, R.d));
-  o.c = cfma(L.c, R.a, cmul(L.d, R.c));
-  o.d = cfma(L.c, R.b, cmul(L.d, R.d));
-  return o;
-}
-
-// Exact power-of-two rescaling: a Moebius matrix acts projectively.
-__device__ inline void mob_norm(Mob& m) {
-  double mx = fmax(fmax(fmax(fabs(m.a.x), fabs(m.a.y)), fmax(fabs(m.b.x), fabs(m.b.y))),
-                   fmax(fmax(fabs(m.c.x), fabs(m.c.y)), fmax(fabs(m.d.x), fabs(m.d.y))));
-  if (mx > 0.0 && mx < INFINITY) {
-    int e;
-    frexp(mx, &e);
-    const double s = ldexp(1.0, -e);
-    m.a = cscale(m.a, s);
-    m.b = cscale(m.b, s);
-    m.c = cscale(m.c, s);
-    m.d = cscale(m.d, s);
-  }
-}
 
 __device__ inline Aff aff_then(const Aff& later, const Aff& earlier) {  // later o earlier
   Aff o;
@@ -328,21 +299,9 @@ __device__ inline RowCoef coef_of_sigma(const LineDev& a, double2 sig) {
   r.dhi = make_double2(sig.x * a.m_end + a.kHi.x / a.hL, sig.y * a.m_end + a.kHi.y / a.hL);
   return r;
 }
-__device__ inline RowCoef row_coef(const LineDev& a, int64_t l, int64_t m) {
-  return coef_of_sigma(a, line_sigma(a, l, m));
-}
 
-__device__ inline double2 diag_of(const RowCoef& r, int x, int nL) {
-  if (x >= nL) return make_double2(1, 0);
-  if (x == 0) return r.dlo;
-  if (x == nL - 1) return r.dhi;
-  return r.dint;
-}
 // First row of lane q: lanes below r own c rows, the others c - 1.
 __host__ __device__ inline int chunk_start(int q, int c, int r) { return q * (c - 1) + (q < r ? q : r); }
-// e(x) = coupling between rows x-1 and x
-__device__ inline bool has_e(int x, int nL) { return x > 0 && x < nL; }
-
 // The lines of a block.  Line index (b, l, m) of slot `sl` at iteration `it`;
 // false past the end of the tile's extent.  Line counts stay below 2^31 (checked
 // at launch), so 32-bit index arithmetic suffices; the divisions (about thirty
