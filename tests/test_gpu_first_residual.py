@@ -35,3 +35,10 @@ def test_entering_pivots(boundary):
     """Pivots that enter a lane's rows as the rows before leave them: 5.8e-12 to
     6.9e-12 in the model (composed in a scan over the lanes 2.7e-11 to 3.8e-11)."""
     assert max(_first_residuals(boundary, (1, 2, 3))) <= 2e-11
+
+
+def test_periodic_spectra():
+    """Periodic eigenvalues right to extended precision, not shifted alike in all
+    modes: 8.8e-14 to 1.2e-13 in the model with the boundary steps in the
+    eigenbasis (with pi rounded to double 3.7e-13 to 4.7e-13)."""
+    assert max(_first_residuals(helm.BOUNDARY_TABLES, (1, 2, 3))) <= 3.5e-13
