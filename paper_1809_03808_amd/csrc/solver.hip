@@ -24,6 +24,7 @@
 #include <cstdlib>
 
 #include "helm_internal.h"
+#include "line_tiles.h"
 
 namespace helm {
 
@@ -184,6 +185,10 @@ struct helm_plan {
   // Workspace generation: raised whenever a workspace buffer moves, so that
   // graphs captured on the old addresses are not launched again.
   uint64_t ws_gen = 0;
+  // right-hand sides and need_r of the last workspace that was ensured (0:
+  // none, or a buffer was lost since)
+  int ws_nb = 0;
+  bool ws_r = false;
   // Captured solve for repeated helm_solve calls on unchanged arguments:
   // the arguments of the previous call and the refinement steps it took,
   // the graph with the arguments it was captured for, and a pinned host
@@ -777,8 +782,7 @@ int red_l_mode(const helm_plan* p) { return p->red_layout; }
 // partial of 2 nL values per block (layout 3: per slot), and R blocks stay
 // resident at once (one 512-thread or two 256-thread blocks per compute unit at
 // the register use of the reducing kernels), so its tiles are those that take
-// the fewest iterations in rounds of R blocks, a block's start and partials
-// counted as 0.7 of an iteration: 512 blocks at 256^3, and not the 516 that
+// the fewest iterations in rounds of R blocks (reduce_tiles): 512 blocks at 256^3, and not the 516 that
 // left four blocks to a second round at 129^3 x 2 (70 us; 774 blocks of two
 // thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us); 410
 // blocks of 5 lines at 2049^2 instead of 257 of 8 (40 + 47 -> 34 + 42 us, the sums
@@ -805,18 +809,7 @@ void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, bool 
   // lines per iteration of a block along the reduced index, and per tile
   const int64_t step = l3 ? 1 : LPB, tmin = l3 ? 1 : std::min<int64_t>(lean ? 8 : 4, extent);
   const int64_t most = lean ? R : 8 * R;  // blocks
-  double best = 1e300;
-  for (int64_t n = 1; n <= extent && (n == 1 || groups * n <= most); ++n) {
-    int64_t t = std::max((extent + n - 1) / n, tmin);
-    t = (t + step - 1) / step * step;
-    const int64_t nt = (extent + t - 1) / t;
-    const double cost = (double)((groups * nt + R - 1) / R) * ((double)(t / step) + 0.7);
-    if (cost < 0.98 * best) {
-      best = cost;
-      *tile = (int)t;
-      *ntiles = (int)nt;
-    }
-  }
+  reduce_tiles(extent, groups, step, tmin, R, most, tile, ntiles);
 }
 
 void tiles_for(const helm_plan* p, int red, int nb, int nO, int nI, int nL, int* tile, int* ntiles) {
@@ -1502,11 +1495,21 @@ std::array<size_t, WS_N> workspace_bytes(const helm_plan* p, int nb, bool fp32, 
 int ensure_workspace_impl(helm_plan* p, int nb, bool fp32, bool need_r);
 
 // Grows the workspace for nb right-hand sides; raises the plan's workspace
-// generation when any buffer moved.
+// generation when any buffer moved.  (Buffers only grow, so the sizes are not
+// worked out again for the call's predecessor.)
 int ensure_workspace(helm_plan* p, int nb, bool fp32, bool need_r) {
+  if (p->ws_nb == nb && p->ws_r == need_r) {
+    p->h_norms.resize(2 * nb);
+    return HELM_OK;
+  }
+  p->ws_nb = 0;
   const auto before = workspace_addrs(p);
   const int rc = ensure_workspace_impl(p, nb, fp32, need_r);
   if (workspace_addrs(p) != before) ++p->ws_gen;
+  if (rc == HELM_OK) {
+    p->ws_nb = nb;
+    p->ws_r = need_r;
+  }
   return rc;
 }
 
@@ -3039,7 +3042,10 @@ int helm_residual(helm_plan* p, const void* u, const void* f, void* r, double* r
                       hipSuccess &&
                   p->norms.ensure((size_t)nrhs * 2 * sizeof(double)) == hipSuccess;
   if (workspace_addrs(p) != before) ++p->ws_gen;
-  if (!ok) return HELM_ENOMEM;
+  if (!ok) {
+    p->ws_nb = 0;  // a buffer that could not grow is gone
+    return HELM_ENOMEM;
+  }
   p->h_norms.resize(2 * nrhs);
   (void)N;
   double mx = 0;
