@@ -208,14 +208,73 @@ struct helm_plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   void* ctl_host = nullptr;
+  // The last launch of graph_exec was not waited for (unchecked solves).
+  bool graph_in_flight = false;
+  // Graphs of earlier arguments that may still run: destroyed once `done`,
+  // recorded behind their last launch, has passed.
+  struct Retired {
+    hipGraph_t graph;
+    hipGraphExec_t exec;
+    hipEvent_t done;  // null: kept until the plan is destroyed
+  };
+  std::vector<Retired> retired;
+  // Destroys retired graphs that have run, waiting for all but the last `keep`.
+  void reap(size_t keep) {
+    for (size_t i = 0; i < retired.size();) {
+      Retired& r = retired[i];
+      if (r.done && retired.size() > keep) (void)hipEventSynchronize(r.done);
+      if (!r.done || hipEventQuery(r.done) != hipSuccess) {
+        (void)hipGetLastError();  // (not ready is reported as an error)
+        ++i;
+        continue;
+      }
+      (void)hipGraphExecDestroy(r.exec);
+      (void)hipGraphDestroy(r.graph);
+      (void)hipEventDestroy(r.done);
+      retired.erase(retired.begin() + (long)i);
+    }
+  }
   void drop_graph() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
     graph_exec = nullptr;
     graph = nullptr;
+    graph_in_flight = false;
   }
-  ~helm_plan() {
+  // Gives up the captured graph, from a call on stream `st`.  One that may still
+  // run is not destroyed under its launch: it waits for an event behind that
+  // launch, so the call stays asynchronous (another stream's launch, whose
+  // stream may be gone, is waited for).
+  void retire_graph(hipStream_t st) {
+    if (graph_exec && graph_in_flight) {
+      if (graph_key.st != st) {
+        (void)hipDeviceSynchronize();
+      } else {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        (void)hipStreamIsCapturing(st, &cap);
+        Retired r{graph, graph_exec, nullptr};
+        if (cap == hipStreamCaptureStatusNone) {
+          reap(1);
+          if (hipEventCreateWithFlags(&r.done, hipEventDisableTiming) != hipSuccess) r.done = nullptr;
+          if (r.done && hipEventRecord(r.done, st) != hipSuccess) {
+            (void)hipEventDestroy(r.done);
+            r.done = nullptr;
+          }
+        }
+        retired.push_back(r);
+        graph = nullptr;
+        graph_exec = nullptr;
+      }
+    }
     drop_graph();
+  }
+  ~helm_plan() {  // (helm_destroy has waited for the device)
+    drop_graph();
+    for (Retired& r : retired) {
+      (void)hipGraphExecDestroy(r.exec);
+      (void)hipGraphDestroy(r.graph);
+      if (r.done) (void)hipEventDestroy(r.done);
+    }
     if (gcap) (void)hipStreamDestroy(gcap);
     if (ctl_host) (void)hipHostFree(ctl_host);
     if (h_norms_pin) (void)hipHostFree(h_norms_pin);
@@ -1827,18 +1886,20 @@ int solve_entry(helm_plan* p, const void* f, void* u, int nrhs, hipStream_t st, 
   double rel = 0;
   bool graph_ran = false;
   if (allow_graph && !p->prof) {
-    if (p->graph_exec && !(p->graph_key == key && p->graph_gen == p->ws_gen)) p->drop_graph();
+    if (p->graph_exec && !(p->graph_key == key && p->graph_gen == p->ws_gen)) p->retire_graph(st);
     if (!p->graph_exec && repeat && prev >= 0) {
       rc = capture_solve(p, F, U, nrhs, st, prev);
       if (rc) return rep.status = rc;
     }
     if (p->graph_exec) {
       if (hipGraphLaunch(p->graph_exec, st) != hipSuccess) return rep.status = HELM_EDEVICE;
+      p->graph_in_flight = true;
       if (!check) {
         p->prev_steps = 0;
         return rep.status = HELM_OK;
       }
       if (hipStreamSynchronize(st) != hipSuccess) return rep.status = HELM_EDEVICE;
+      p->graph_in_flight = false;
       IrCtl c;
       std::memcpy(&c, p->ctl_host, sizeof(IrCtl));
       graph_ran = true;
@@ -3133,6 +3194,10 @@ int helm_batch_solve(helm_batch* b, const void* const* f, void* const* u, const 
   for (int i = 0; same && i < n; ++i)
     same = b->kf[i] == f[i] && b->ku[i] == u[i] && b->kn[i] == nrhs[i] && b->kgen[i] == b->plans[i]->ws_gen;
   if (!same) {
+    // The last launch may still run: it is not left without its graph, and the
+    // solves below take the same workspaces, also from another stream.
+    if (b->exec && (b->last == st ? hipStreamSynchronize(st) : hipDeviceSynchronize()) != hipSuccess)
+      return HELM_EDEVICE;
     b->drop_graph();
     // Eager solves first: they create every lazily built table (twiddles,
     // chirps) outside the capture and give the refinement depth to capture:
