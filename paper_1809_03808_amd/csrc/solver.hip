@@ -2076,7 +2076,12 @@ std::string tune_key(const helm_plan* p) {
 }
 
 // Value of `field` (e.g. "transform=") on the last cache line for this key.
-bool tune_lookup(const std::string& path, const std::string& key, const char* field, int* value) {
+// `measured`, if given, is what a line with measured times has to hold besides:
+// times of something else (an earlier version's operator tables, a convolution
+// of another length) decide nothing here.  Lines without times are taken as set
+// by hand.
+bool tune_lookup(const std::string& path, const std::string& key, const char* field, int* value,
+                 const char* measured = nullptr) {
   FILE* f = std::fopen(path.c_str(), "r");
   if (!f) return false;
   const std::string pre = "helm-tune " + key + " " + field;
@@ -2084,6 +2089,7 @@ bool tune_lookup(const std::string& path, const std::string& key, const char* fi
   bool found = false;
   while (std::fgets(line, sizeof line, f)) {
     if (std::strncmp(line, pre.c_str(), pre.size()) != 0) continue;
+    if (measured && std::strstr(line, "_ms") && !std::strstr(line, measured)) continue;
     *value = std::atoi(line + pre.size());
     found = true;  // the last matching line wins
   }
@@ -2525,8 +2531,11 @@ int tune_chirp(helm_plan* p) {
     if (!A.blue || A.Mnbp == 1 || !onepass_length(A.M)) continue;  // (Mnbp = 1: one pass is the only form)
     char field[16];
     std::snprintf(field, sizeof field, "chirp%d=", j);
+    char length[24];
+    std::snprintf(length, sizeof length, " M=%d ", A.M);
     int cached = -1;
-    if (!p->tune_path.empty() && tune_lookup(p->tune_path, key, field, &cached) && (cached == 0 || cached == 1)) {
+    if (!p->tune_path.empty() && tune_lookup(p->tune_path, key, field, &cached, length) &&
+        (cached == 0 || cached == 1)) {
       A.onepass = cached;
       continue;
     }
@@ -2571,8 +2580,8 @@ int tune_chirp(helm_plan* p) {
     if (!p->tune_path.empty()) {
       FILE* f = std::fopen(p->tune_path.c_str(), "a");
       if (f) {
-        std::fprintf(f, "helm-tune %s %s%d multipass_ms=%.6g onepass_ms=%.6g\n", key.c_str(), field, A.onepass,
-                     best[0], best[1]);
+        std::fprintf(f, "helm-tune %s %s%d%smultipass_ms=%.6g onepass_ms=%.6g\n", key.c_str(), field, A.onepass,
+                     length, best[0], best[1]);
         std::fclose(f);
       }
     }
@@ -2592,9 +2601,9 @@ int setup_boundary_tables(helm_plan* p) {
   if (!forced && (double)modal_bytes(p) > budget) return HELM_OK;
   const std::string key = tune_key(p);
   int cached = -1;
-  if (!forced && !p->tune_path.empty() && tune_lookup(p->tune_path, key, "boundary cap_min_nb=", &cached) &&
-      cached == 0)
-    return HELM_OK;  // measured before: the tables never pay for this shape
+  if (!forced && !p->tune_path.empty() &&
+      tune_lookup(p->tune_path, key, "boundary cap_min_nb=", &cached, " eigenbasis_ms_1=") && cached == 0)
+    return HELM_OK;  // measured before: the eigenbasis never pays for this shape
   int rc = build_modal(p);
   // no usable eigenbasis (or, unless asked for, no memory for it): line sweeps
   if (rc == HELM_ENOCONV || (rc == HELM_ENOMEM && !forced)) {
@@ -2630,8 +2639,8 @@ int setup_boundary_tables(helm_plan* p) {
   if (!p->tune_path.empty()) {
     FILE* f = std::fopen(p->tune_path.c_str(), "a");
     if (f) {
-      std::fprintf(f, "helm-tune %s boundary cap_min_nb=%d lines_ms_1=%.6g lines_ms_16=%.6g tables_ms_1=%.6g "
-                   "tables_ms_16=%.6g\n", key.c_str(), nmin, ms[0], ms[1], ms[2], ms[3]);
+      std::fprintf(f, "helm-tune %s boundary cap_min_nb=%d lines_ms_1=%.6g lines_ms_16=%.6g eigenbasis_ms_1=%.6g "
+                   "eigenbasis_ms_16=%.6g\n", key.c_str(), nmin, ms[0], ms[1], ms[2], ms[3]);
       std::fclose(f);
     }
   }
