@@ -156,7 +156,7 @@ struct helm_plan {
                 *mG1 = nullptr, *mG2 = nullptr;
   int modal_min_nb = 0;
   int red_layout = 2;  // layout of the line reductions over the outer modes (2 or 3)
-  bool lean_parts = false;  // fewest partial sums (solves in the fixed static scratch that would not fit otherwise)
+  bool lean_parts = false;  // fewest partial sums, for the right-hand sides of the current solve (set_lean)
   int fft_small = 0;   // 512-point passes: 0 the 128 KB tile, 1 the 64 KB complex64 tile, 2 streaming (tuned)
   double modal_ms[4] = {-1, -1, -1, -1};  // measured: lines at 1 and 16 RHS, tables at 1 and 16 RHS
   std::string tune_path;
@@ -846,7 +846,8 @@ int red_l_mode(const helm_plan* p) { return p->red_layout; }
 // thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us); 410
 // blocks of 5 lines at 2049^2 instead of 257 of 8 (40 + 47 -> 34 + 42 us, the sums
 // of the partials 2 us more).
-// `lean` keeps to the partials of one round of blocks, of at least 8 lines.
+// `lean` keeps to the partials of one round of blocks, of at least 8 lines
+// (set_lean).
 // Other launches take up to 2048 blocks.
 void tiles_for_layout(int red, int layout, int nb, int nO, int nI, int nL, bool lean, int* tile, int* ntiles) {
   int P, c, NT;
@@ -1551,6 +1552,27 @@ std::array<size_t, WS_N> workspace_bytes(const helm_plan* p, int nb, bool fp32, 
   return w;
 }
 
+size_t round256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Bytes of the fixed scratch that a solve of nb right-hand sides takes.
+size_t static_bytes(const helm_plan* p, int nb) {
+  const bool mixed = p->opt.precision == HELM_PREC_MIXED;
+  size_t total = 0;
+  for (size_t b : workspace_bytes(p, nb, mixed, mixed || p->opt.check)) total += round256(b);
+  return total;
+}
+
+// Sets whether solves of nb right-hand sides keep to the fewest partial sums:
+// where they would not fit the fixed scratch of helm_solve_static otherwise
+// (more are faster, but never refuse a call).  The same for every entry point,
+// which thus add in the same order.
+void set_lean(helm_plan* p, int nb) {
+  p->lean_parts = false;
+  if (nb > HELM_STATIC_MAX_RHS || static_bytes(p, nb) <= (size_t)HELM_STATIC_SCRATCH_BYTES) return;
+  p->lean_parts = true;
+  p->lean_parts = static_bytes(p, nb) <= (size_t)HELM_STATIC_SCRATCH_BYTES;
+}
+
 int ensure_workspace_impl(helm_plan* p, int nb, bool fp32, bool need_r);
 
 // Grows the workspace for nb right-hand sides; raises the plan's workspace
@@ -1562,6 +1584,7 @@ int ensure_workspace(helm_plan* p, int nb, bool fp32, bool need_r) {
     return HELM_OK;
   }
   p->ws_nb = 0;
+  set_lean(p, nb);
   const auto before = workspace_addrs(p);
   const int rc = ensure_workspace_impl(p, nb, fp32, need_r);
   if (workspace_addrs(p) != before) ++p->ws_gen;
@@ -1976,16 +1999,14 @@ int static_workspace(int dev, void** out) {
   return HELM_OK;
 }
 
-size_t round256(size_t b) { return (b + 255) / 256 * 256; }
-
 // The plan's workspace buffers pointed into the static array for the scope
 // of one solve, then restored (the plan's own buffers and captured graphs
 // are untouched).
 struct StaticWorkspace {
   helm_plan* p;
   std::array<std::pair<void*, size_t>, WS_N> saved;
-  bool prof;
-  StaticWorkspace(helm_plan* pl, const std::array<size_t, WS_N>& w) : p(pl) {
+  bool prof, lean;
+  StaticWorkspace(helm_plan* pl, const std::array<size_t, WS_N>& w, bool lean_before) : p(pl), lean(lean_before) {
     const auto b = ws_bufs(p);
     char* base = static_cast<char*>(p->static_ws);
     size_t off = 0;
@@ -2008,7 +2029,7 @@ struct StaticWorkspace {
     }
     p->prof = prof;
     p->no_alloc = false;
-    p->lean_parts = false;
+    p->lean_parts = lean;
   }
 };
 
@@ -2028,20 +2049,16 @@ int solve_static(helm_plan* p, const void* f, void* u, int nrhs, hipStream_t st)
   rep.rel_residual_max = -1;
   rep.rel_residual_first = -1;
   if (nrhs > HELM_STATIC_MAX_RHS) return rep.status = HELM_ENOMEM;
-  std::array<size_t, WS_N> w{};
+  const bool lean = p->lean_parts;
+  set_lean(p, nrhs);
+  const auto w = workspace_bytes(p, nrhs, mixed, check);
   size_t total = 0;
-  for (int lean = 0; lean < 2; ++lean) {  // more partial sums are faster, but never refuse a call
-    p->lean_parts = lean != 0;
-    w = workspace_bytes(p, nrhs, mixed, check);
-    total = 0;
-    for (size_t b : w) total += round256(b);
-    if (total <= (size_t)HELM_STATIC_SCRATCH_BYTES) break;
-  }
+  for (size_t b : w) total += round256(b);
   if (total > (size_t)HELM_STATIC_SCRATCH_BYTES) {
-    p->lean_parts = false;
+    p->lean_parts = lean;
     return rep.status = HELM_ENOMEM;
   }
-  StaticWorkspace ws(p, w);
+  StaticWorkspace ws(p, w, lean);
   const double2* F = reinterpret_cast<const double2*>(f);
   double2* U = reinterpret_cast<double2*>(u);
   int rc = solve_once(p, f, ST_C128, U, 0, nrhs, mixed, st);
