@@ -2286,9 +2286,10 @@ int measure_boundary(helm_plan* p, int nb, double* t_lines, double* t_modal) {
 
 // Layout of the line reductions over the outer modes (3D): fixed by
 // HELM_RED_L_LAYOUT (2 or 3) when set, else the cached decision, else the
-// faster of the two on an outer-Step-1 sweep of one right-hand side (read of
-// an N-sized input, generated rank-2 term, weighted sums over l; best of 3
-// after a warm-up), appended to the cache.
+// faster of the two on the sweep that the plan's solves make, with one right-hand
+// side: the plain reduction of an N-sized input with the boundary steps in the
+// eigenbasis (the kernel that prefetches), else that of outer Step 1 with its
+// generated rank-2 term (best of 3 after a warm-up), appended to the cache.
 int tune_layout(helm_plan* p) {
   const char* env = std::getenv("HELM_RED_L_LAYOUT");
   if (env && (env[0] == '2' || env[0] == '3') && env[1] == 0) {
@@ -2324,10 +2325,14 @@ int tune_layout(helm_plan* p) {
   la.piv = p->seed[0];
   la.in = in.p;
   la.in_kind = fp32 ? ST_C64 : ST_C128;
-  la.PI = pi.p;  // in the storage type of the lines (filled with finite bytes either way)
+  la.real_sigma = true;
+  const bool plain = p->modal_min_nb > 0;
+  if (!plain) {
+    la.PI = pi.p;  // in the storage type of the lines (filled with finite bytes either way)
+    la.beta0 = A2.genB0;
+    la.beta1 = A2.genB1;
+  }
   la.r2_kind = la.in_kind;
-  la.beta0 = A2.genB0;
-  la.beta1 = A2.genB1;
   la.rho0 = A1.redB0;
   la.rho1 = A1.redB1;
   la.part = part.as<double2>();
@@ -2360,8 +2365,8 @@ int tune_layout(helm_plan* p) {
   if (!p->tune_path.empty()) {
     FILE* f = std::fopen(p->tune_path.c_str(), "a");
     if (f) {
-      std::fprintf(f, "helm-tune %s layout=%d layout2_ms=%.6g layout3_ms=%.6g\n", key.c_str(), p->red_layout,
-                   best[0], best[1]);
+      std::fprintf(f, "helm-tune %s layout=%d launch=%s layout2_ms=%.6g layout3_ms=%.6g\n", key.c_str(),
+                   p->red_layout, plain ? "plain" : "rank2", best[0], best[1]);
       std::fclose(f);
     }
   }
@@ -3054,10 +3059,6 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
     }
     if (hipDeviceSynchronize() != hipSuccess) return HELM_EDEVICE;
   }
-  if (dim == 3 && tf != HELM_TRANSFORM_DENSE) {
-    const int lrc = tune_layout(p.get());
-    if (lrc != HELM_OK) return lrc;
-  }
   if (want_tab) {
     const int brc = setup_boundary_tables(p.get());
     if (brc != HELM_OK) return brc;
@@ -3068,6 +3069,10 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
     }
   }
   if (tf != HELM_TRANSFORM_DENSE) {
+    if (dim == 3) {
+      const int lrc = tune_layout(p.get());
+      if (lrc != HELM_OK) return lrc;
+    }
     const int frc = tune_fft_tile(p.get());
     if (frc != HELM_OK) return frc;
     const int prc = tune_pow2(p.get());

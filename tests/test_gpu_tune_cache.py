@@ -50,3 +50,11 @@ def test_decisions_without_times_are_taken(tmp_path):
     cache.write_text(f"{key} boundary cap_min_nb=3\n{key} chirp0=1\n{key} chirp1=0\n")
     _setup(grid, cache)
     assert len(_lines(cache, " boundary ")) == 1 and len(_lines(cache, " chirp")) == 2
+
+
+@pytest.mark.parametrize("boundary,launch", [(helm.BOUNDARY_TABLES, "plain"), (helm.BOUNDARY_LINES, "rank2")])
+def test_layout_timed_on_the_launch_of_the_solves(boundary, launch, tmp_path):
+    cache = tmp_path / "tune.txt"
+    _setup((24, 20, 22), cache, boundary=boundary)
+    lines = _lines(cache, " layout=")
+    assert len(lines) == 1 and f" launch={launch} " in lines[0]
