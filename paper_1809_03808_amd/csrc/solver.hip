@@ -94,6 +94,7 @@ struct PAxis {
   // Mna * Mnbp (setup_bluestein).
   int blue = 0, M = 0, Mna = 0, Mnbp = 0;
   int onepass = 0;  // the whole chirp-z convolution in one pass (tuned)
+  int inv_fp64 = 0; // inverse chirp-z transforms of complex64 lines in FP64 arithmetic (setup_bluestein)
   DevMem btab;
   const void* chirp_d[2] = {nullptr, nullptr};  // w for sign -1, +1 (double2[n])
   const void* chirp_f[2] = {nullptr, nullptr};  // same in float2
@@ -434,7 +435,16 @@ void pow2_split(int L, int* na, int* nb) {
 // above 512 split into two factors; 9 * 2^j >= 576 into nb (the passes that
 // carry the chirps, a power of two, 64 <= nb <= 512) times na = 9 * 2^k <= 72
 // (the convolution pass); 72, 144 and 288 only run as one pass.
-int setup_bluestein(PAxis& a) {
+// The rounding errors of a convolution spread evenly over its M rows, so the
+// error of the n rows that are kept grows as (n / M)^(1/2): in complex64 the rows
+// saved below 576 (n <= 145) cost 20 to 30% more error (n = 129: 1.24e-7 of the
+// transform with M = 512, 1.51e-7 with 256; from 257 nodes on, M = 512 for 576 and
+// so on, none).  Mixed plans take the inverse transforms of these axes, whose
+// error the residual sees amplified, in FP64 arithmetic on complex64 lines (first
+// and refined residual of 129^3 x 2: 9.7e-7 and 3.8e-13 with M = 512, 1.2e-6 and
+// 5.4e-13 with 256, now 3.0e-7 and 8.2e-14, for 936 -> 983 us a solve; M = 512 takes
+// 1281; the forward ones in FP64 too 1005 us, 2.0e-7 and 2.0e-14).
+int setup_bluestein(PAxis& a, bool mixed) {
   const int n = a.n;
   int M = 1;
   while (M < 2 * n - 2) M <<= 1;
@@ -451,6 +461,9 @@ int setup_bluestein(PAxis& a) {
     pow2_split(M, &a.Mna, &a.Mnbp);
   }
   a.M = M;
+  int Mp = 1;  // power of two for 2n - 1 rows
+  while (Mp < 2 * n - 1) Mp <<= 1;
+  a.inv_fp64 = mixed && M <= 288 && M < Mp;
   std::vector<double2> hd((size_t)2 * n + 2 * M);
   std::vector<float2> hf((size_t)2 * n + 2 * M);
   for (int si = 0; si < 2; ++si) {
@@ -650,6 +663,7 @@ int run_fft(helm_plan* p, const PAxis& a, int sign, bool fp32, const void* in, i
                     nullptr, accumulate, tmp, tmp_kind, skip, st, a.half_tile);
   (void)tmp;
   (void)tmp_kind;
+  if (sign > 0 && a.inv_fp64) fp32 = false;
   const int si = sign < 0 ? 0 : 1;
   const int T = fp32 ? ST_C64 : ST_C128;
   const int64_t n = a.n, M = a.M;
@@ -2962,7 +2976,7 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
       pow2_split(a.n, &a.na, &a.nbp);
       if (a.na > 512 || a.nbp > 512) return HELM_EUNSUPPORTED;
     } else {
-      const int bst = setup_bluestein(a);
+      const int bst = setup_bluestein(a, p->opt.precision == HELM_PREC_MIXED);
       if (bst != HELM_OK) return bst;
     }
     std::vector<cd> vfull, lamlo;
