@@ -83,9 +83,14 @@ __device__ void ir_update(const double* norms, int nb, const IrCheck& k) {
 // floor of a graph node) out of a small solve.
 // Ordering across the XCDs: the partials are agent-scope atomic stores, which
 // write through the XCD's L2, and the wave waits for them before it counts its
-// block; the last block reads them with agent-scope atomic loads.  A release
-// fence instead of the wait writes back the whole L2 once per block (4096^2
-// mixed: 139 -> 227 us per launch).
+// block (on gfx9 targets vmcnt counts stores, and one has left when it is counted
+// off; targets with a store counter of their own would need another wait); the
+// last block, and only it, has an acquire fence before it reads them with
+// agent-scope atomic loads.  A release fence instead of the wait writes back the
+// whole L2 once per block (4096^2 mixed: 139 -> 227 us per launch).
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "the hand-over of the norms is written for gfx950"
+#endif
 template <int NT>
 __device__ inline void finish_norms(const ResidArgs& a, double (*red)[NT], double sr, double sf, int64_t bid,
                                     int64_t blocks_per_rhs) {
@@ -113,6 +118,7 @@ __device__ inline void finish_norms(const ResidArgs& a, double (*red)[NT], doubl
   if (!a.counter) return;
   __syncthreads();
   if (!last) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const int lane = tid & 63, wv = tid >> 6;
   for (int64_t b = wv; b < a.nb; b += NT / 64) {
     double r = 0.0, f = 0.0;
