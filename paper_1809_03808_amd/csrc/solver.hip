@@ -440,10 +440,12 @@ void pow2_split(int L, int* na, int* nb) {
 // saved below 576 (n <= 145) cost 20 to 30% more error (n = 129: 1.24e-7 of the
 // transform with M = 512, 1.51e-7 with 256; from 257 nodes on, M = 512 for 576 and
 // so on, none).  Mixed plans take the inverse transforms of these axes, whose
-// error the residual sees amplified, in FP64 arithmetic on complex64 lines (first
-// and refined residual of 129^3 x 2: 9.7e-7 and 3.8e-13 with M = 512, 1.2e-6 and
-// 5.4e-13 with 256, now 3.0e-7 and 8.2e-14, for 936 -> 983 us a solve; M = 512 takes
-// 1281; the forward ones in FP64 too 1005 us, 2.0e-7 and 2.0e-14).
+// error the residual sees amplified, in FP64 arithmetic on complex64 lines.  Where
+// both axes of a 3D plan take powers of two, the error of one inverse transform is
+// less than that of two with the longer lengths, and only x_2 does (setup_impl).
+// First and refined residual of 129^3 x 2: 9.7e-7 and 3.8e-13 with M = 512, 1281 us a
+// solve; 1.2e-6 and 5.4e-13 with 256, 940 us; now 8.8e-7 and 3.3e-13, 962 us (both
+// inverse ones 3.0e-7 and 8.3e-14, 983 us; all four 2.0e-7 and 2.0e-14, 1005 us).
 int setup_bluestein(PAxis& a, bool mixed) {
   const int n = a.n;
   int M = 1;
@@ -3034,6 +3036,8 @@ int setup_impl(int dim, const int64_t* grid, const double* h, double c, long dou
     a.va1d = t + 7 * a.n;
     a.invmu = reinterpret_cast<double*>((char*)a.tab.p + nb2);
   }
+  auto halved = [](const PAxis& a) { return a.inv_fp64 && is_pow2(a.M); };
+  if (dim == 3 && halved(p->ax[0]) && halved(p->ax[1])) p->ax[0].inv_fp64 = 0;
   // Line-matrix families (outer branch, inner branch): the shift
   // sigma = lambda_outer + lambda_inner - w^2 of every line, formed in extended
   // precision and rounded once (near-resonant modes would otherwise lose
