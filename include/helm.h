@@ -85,9 +85,9 @@ extern "C" {
  *           eigenvectors of the last axis and the Step-2 maps of every mode,
  *           16 (2 n_3^2 + 2 n_2^2 + 3 (n_1 + n_2) n_3) bytes): three sweeps of the
  *           grid and products of boundary vectors remain.  A last axis without
- *           a well-conditioned eigenbasis (coinciding eigenvalues: an axis with
- *           both faces absorbing at about 3 points per wavelength and below)
- *           takes LINES;
+ *           a well-conditioned eigenbasis (both faces absorbing, from about 3 to
+ *           3.7 points per wavelength, or coinciding eigenvalues below) takes
+ *           LINES;
  *   AUTO    build the tables when they fit the memory budget (at most 32 GiB
  *           and a quarter of the free device memory) and use them for solves
  *           of at least as many right-hand sides as the plan measured them to
@@ -304,15 +304,15 @@ void helm_destroy(helm_plan* p);
  * helm_batch_solve -- u[i] = A_i^{-1} f[i] for every plan i, nrhs[i] <= max_nrhs
  *   right-hand sides each, same layout and ownership as helm_solve.  On the
  *   first call, or when any pointer, count or the stream differs from the
- *   previous call, it solves each problem once eagerly on `stream` (this also
- *   sets the refinement depth: one step more than those inputs needed, at
- *   least 2, at most the plan's max_iter), then captures every problem's
- *   complete solve into one graph, the problems on parallel branches, and
- *   instantiates it.  Every call then launches that graph on `stream` and
- *   returns without synchronising.  Checked plans (mixed precision, or
- *   opt.check) refine under device control: a residual check kernel stops
- *   the refinement of a problem by raising a flag that makes its remaining
- *   launches return at once.
+ *   previous call, it waits for the launch of the previous call and solves
+ *   each problem once eagerly on `stream` (this also sets the refinement
+ *   depth: one step more than those inputs needed, at least 2, at most the
+ *   plan's max_iter), then captures every problem's complete solve into one
+ *   graph, the problems on parallel branches, and instantiates it.  Every call
+ *   then launches that graph on `stream` and returns without synchronising.
+ *   Checked plans (mixed precision, or opt.check) refine under device control:
+ *   a residual check kernel stops the refinement of a problem by raising a
+ *   flag that makes its remaining launches return at once.
  *   Errors: HELM_EINVAL, HELM_ENOMEM, HELM_EDEVICE, or the status of a
  *   failing eager solve.
  *

@@ -142,7 +142,7 @@ hipError_t launch_fft_pass(const FftPass& p, bool fp32, const void* in, void* ou
 //   red == 1: part[((b nO + l) ntiles + t)][k][:] = sum_{m in tile t} rho_k[m] y
 //   red == 2: part[((b nI + m) ntiles + t)][k][:] = sum_{l in tile t} rho_k[l] y
 //   red == 3: the sums of red == 2 with the lines of a block taken as
-//             consecutive m at one l per iteration (all l in one tile)
+//             consecutive m at one l per iteration
 // ---------------------------------------------------------------------------
 struct LineArgs {
   int nb = 1, nO = 1, nI = 1, nL = 0;
@@ -355,7 +355,7 @@ struct ResidArgs {
   const double2* f;
   void* r;        // nullable
   int r_kind;     // ST_C128 / ST_C64
-  double* norms;  // device [nb][2]: sum |r|^2, sum |f|^2 (accumulated by the finishing kernel)
+  double* norms;  // device [nb][2]: sum |r|^2, sum |f|^2 (written by the last block or the finishing kernel)
   double* scratch;
   int64_t scratch_len;
   const int* skip = nullptr;  // device flag: nothing is computed while *skip != 0

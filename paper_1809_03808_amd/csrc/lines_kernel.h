@@ -431,7 +431,8 @@ __device__ inline int stage_pos(int e) { return e + (e >> 3); }
 // and folds it into its backward map, which becomes the constant map to the
 // value entering its chunk from above.
 // Storing launches are held to 128 registers where LDS admits four waves per
-// SIMD and the kernel comes close: exact lines of 16 to 64 and of 512 lanes.
+// SIMD and the kernel comes close: exact lines of 16 to 64 lanes, exact and
+// balanced ones of 512.
 //
 // SPEC: sigma is real (the periodic branch of every periodised axis), so the
 // off-diagonal entry and its square are (a complex product with them takes two

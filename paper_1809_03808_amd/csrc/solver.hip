@@ -1759,9 +1759,10 @@ void fill_axis_tables_host(PAxis& a, long double czx, std::vector<double2>& buf,
 
 // ---------------------------------------------------------------------------
 // Refinement controlled on the device, for solves captured in a graph: the
-// host cannot inspect residual norms between the steps, so a one-thread
-// kernel evaluates them and raises a flag that turns every later launch of
-// the same problem into an immediate return.
+// host cannot inspect residual norms between the steps, so the last block of a
+// residual launch of up to 4096 blocks evaluates them, or a one-thread kernel
+// behind a larger one (stencil.hip), and raises a flag that turns every later
+// launch of the same problem into an immediate return.
 // ---------------------------------------------------------------------------
 __global__ void ir_reset_kernel(IrCtl* c, int done) {
   c->done = done;
