@@ -20,6 +20,15 @@ namespace {
 
 using namespace linek;
 
+// 1/a: a reciprocal with one Newton step in double-double (by long division the
+// factor table of 4096^2 took 3.5 ms a family, so 1.8).
+__device__ inline cdd cdd_rcp(cdd a) {
+  const dd den = dd_add(dd_mul(a.re, a.re), dd_mul(a.im, a.im));
+  const double r0 = rcp_nr(den.hi);
+  const dd r = dd_add(dd_of(r0), dd_mul_d(dd_sub(dd_of(1.0), dd_mul_d(den, r0)), r0));
+  return {dd_mul(a.re, r), dd_neg(dd_mul(a.im, r))};
+}
+
 // Factor table: for every line matrix (l, m) and lane chunk q, the reciprocal
 // pivot entering the chunk of the Thomas elimination, 1/p_x = 1 / (d_x - e^2 / p_{x-1})
 // over the rows before it.  One thread per line, once per plan, in double-double
@@ -29,20 +38,20 @@ using namespace linek;
 // reach the table.  (Composed in FP64 as 2 x 2 Moebius maps in a scan over the
 // chunks, they were most of the residual of a plain FP64 solve: 256^3 at 10 points
 // per wavelength 7.0e-11 with line sweeps and 7.4e-11 with the boundary steps in the
-// eigenbasis, which does not share them, now 8.7e-13 and 9.7e-13; 4096^2 3.1e-9,
-// now 4.8e-11, and 5.2e-11 with the recurrence in FP64.)
+// eigenbasis, which does not share them, now 6.2e-13 and 1.3e-13; 512^3 1.3e-10, now
+// 2.0e-12; 4096^2 3.1e-9, now 4.5e-11, and 5.6e-11 with the recurrence in FP64.)
 __global__ __launch_bounds__(64) void factor_kernel(LineDev a, int P, int64_t lines, double2* piv) {
   const int64_t line = (int64_t)blockIdx.x * 64 + threadIdx.x;  // l * nI + m
   if (line >= lines) return;
   const RowCoef rc = coef_of_sigma(a, line_sigma(a, line / a.nI, line % a.nI));
   double2* out = piv + line * P;
   out[0] = make_double2(0, 0);
-  const cdd one = cdd_of(make_double2(1, 0)), e2 = cdd_of(rc.off2);
+  const cdd e2 = cdd_of(rc.off2);
   cdd ip = cdd_zero();
   int x = 0;
   for (int q = 1; q < P; ++q) {
     for (const int end = chunk_start(q, a.c, a.r); x < end; ++x)
-      ip = cdd_div(one, cdd_sub(cdd_of(x == 0 ? rc.dlo : rc.dint), cdd_mul(e2, ip)));
+      ip = cdd_rcp(cdd_sub(cdd_of(x == 0 ? rc.dlo : rc.dint), cdd_mul(e2, ip)));
     out[q] = make_double2(ip.re.hi, ip.im.hi);
   }
 }
