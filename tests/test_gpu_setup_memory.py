@@ -2,6 +2,8 @@
 default forms: setup needs no more memory than its own tables and the timing of
 the line sweeps."""
 
+import gc
+
 import pytest
 
 from paper_1809_03808_amd import helm, inputs
@@ -17,9 +19,14 @@ def test_forms_that_cannot_be_timed(tmp_path):
     # passes of the 1024-point axis
     grid = (1024, 64, 512)
     cache = tmp_path / "tune.txt"
-    torch.cuda.synchronize()
-    free, _ = torch.cuda.mem_get_info()
-    held = torch.empty(free - 1400 * MB, dtype=torch.uint8, device="cuda")
+    gc.collect()
+    torch.cuda.empty_cache()  # (torch would give cached blocks back in need)
+    held = []
+    for _ in range(4):  # (the runtime gives back memory of its own on a large allocation)
+        free, _ = torch.cuda.mem_get_info()
+        if free > 1410 * MB:
+            held.append(torch.empty(free - 1400 * MB, dtype=torch.uint8, device="cuda"))
+    assert torch.cuda.mem_get_info()[0] <= 1450 * MB
     try:
         plan = helm.Plan(grid, (1.0 / 1023,) * 3, inputs.omega_for_ppw(1024, 10.0), boundary=helm.BOUNDARY_LINES,
                          tune_cache=str(cache))
