@@ -857,11 +857,11 @@ int red_l_mode(const helm_plan* p) { return p->red_layout; }
 // partial of 2 nL values per block (layout 3: per slot), and R blocks stay
 // resident at once (one 512-thread or two 256-thread blocks per compute unit at
 // the register use of the reducing kernels), so its tiles are those that take
-// the fewest iterations in rounds of R blocks (reduce_tiles): 512 blocks at 256^3, and not the 516 that
-// left four blocks to a second round at 129^3 x 2 (70 us; 774 blocks of two
-// thirds the lines 59 us; in layout 3 884 blocks 56 us, 510 blocks 49 us); 410
-// blocks of 5 lines at 2049^2 instead of 257 of 8 (40 + 47 -> 34 + 42 us, the sums
-// of the partials 2 us more).
+// the fewest iterations in rounds of R blocks (reduce_tiles): 512 blocks at
+// 256^3, and not the 516 that left four blocks to a second round at 129^3 x 2
+// (70 us; 774 blocks of two thirds the lines 59 us; in layout 3 884 blocks 56 us,
+// 510 blocks 49 us); 410 blocks of 5 lines at 2049^2 instead of 257 of 8
+// (40 + 47 -> 34 + 42 us, the sums of the partials 2 us more).
 // `lean` keeps to the partials of one round of blocks, of at least 8 lines
 // (set_lean).
 // Other launches take up to 2048 blocks.
